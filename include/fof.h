@@ -79,7 +79,9 @@ typedef struct {
     int32_t predicate;       /* fof_predicate */
     int32_t strict_less;     /* 0: link iff r2 <= l2 (default); 1: r2 < l2 */
     double cell_factor;      /* cell side in units of l_x (>= 1); 0 picks cells of about one
-                                particle each, never narrower than l_x */
+                                particle each, never narrower than l_x, which the search
+                                subdivides where they are much wider than l_x and the limits and
+                                the workspace allow (changes speed only) */
     int32_t collect_stats;   /* 1: count pair tests, links, band hits, CAS retries (slower) */
     int32_t dense_min;       /* cells holding at least this many particles are searched by whole
                                 wavefronts (64 particles against broadcast candidates); the others
@@ -122,7 +124,7 @@ typedef struct {
 
 typedef struct {
     int64_t n_particles;     /* particles in the last build */
-    int64_t n_cells;         /* cells over all boxes */
+    int64_t n_cells;         /* cells over all boxes (of the search, subdivided where it does) */
     int64_t n_groups;        /* groups over all boxes (after finalize) */
     int64_t pair_tests;      /* candidate pairs tested        (collect_stats only) */
     int64_t links;           /* pairs found linked            (collect_stats only) */
@@ -142,7 +144,8 @@ typedef struct {
 
 /* Geometry and FP32 decision thresholds the library uses for one box. */
 typedef struct {
-    int64_t cells_per_axis;  /* n_c: cells of side L / n_c per axis */
+    int64_t cells_per_axis;  /* n_c: cells of side L / n_c per axis (automatic cells: before the search
+                                subdivides them) */
     double l2;               /* l_x * l_x, rounded once (the double predicate's threshold) */
     float lo32;              /* FP32 squared distance below this: linked, proven */
     float hi32;              /* FP32 squared distance above this: not linked, proven */

@@ -194,6 +194,28 @@ fof_status cells_per_axis(const fof_options &o, int64_t n_box, double L, double 
     return FOF_OK;
 }
 
+// Cells per axis the search itself uses. Automatic cells of about one particle
+// are several l_x wide when groups are sparse on average (5 l_x at b = 0.2),
+// and a cell inside a halo then holds thousands of particles, all tested
+// against all. Cells are indexed by rank, so empty ones cost only 2 bits: with
+// automatic cells the search subdivides them to 1.375 l_x, the side the sweep
+// over 1 .. 4 l_x found best for clustered boxes, as far as kRefineCells cells
+// per particle (16 bytes of occupancy words each, a sixth of the workspace)
+// and the 2048 cells per axis allow. A cell factor given by the caller is
+// taken as it is.
+constexpr double kRefineSide = 1.375;
+constexpr double kRefineCells = 64.0;
+
+int64_t search_cells_per_axis(const fof_options &o, int64_t n_box, double L, double lx, int64_t nc)
+{
+    if (o.cell_factor > 0.0 || n_box < 1) return nc;
+    double want = std::floor(L / (kRefineSide * lx));
+    const double most = std::floor(std::cbrt(kRefineCells * (double)n_box));
+    if (want > most) want = most;
+    if (want > kMaxCellsPerAxis) want = kMaxCellsPerAxis;
+    return want > (double)nc ? (int64_t)want : nc;
+}
+
 // FP32 decision thresholds. With u = 2^-24 the FP32 squared distance R32 of a
 // pair satisfies (1-u)^5 R <= R32 <= (1+u)^5 R, R being the exact squared
 // minimum-image distance (one rounding per axis difference, three in the
@@ -254,13 +276,16 @@ void sub_cells(double L, int64_t nc, double lx, int32_t *k_out, int32_t *adj_out
 int dense_min_of(const fof_options &o) { return o.dense_min > 0 ? o.dense_min : kDefaultDenseMin; }
 
 // Validates one box (nb particles, side L, linking length l) and fills its
-// descriptor, cells starting at global cell `cell_base`.
-fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, int64_t cell_base, BoxDev *out)
+// descriptor, cells starting at global cell `cell_base`; `refine`: on the
+// search's own grid (search_cells_per_axis).
+fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, int64_t cell_base, bool refine,
+                        BoxDev *out)
 {
     if (!(L > 0.0) || !std::isfinite(L) || !(l > 0.0) || !std::isfinite(l)) return FOF_ERR_INVALID_ARG;
     int64_t nc = 0;
     fof_status st = cells_per_axis(o, nb, L, l, &nc);
     if (st != FOF_OK) return st;
+    if (refine) nc = search_cells_per_axis(o, nb, L, l, nc);
     BoxDev &b = *out;
     std::memset(&b, 0, sizeof(b));
     b.cell_base = cell_base;
@@ -361,8 +386,8 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     return FOF_OK;
 }
 
-fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx, int32_t n_boxes,
-                     HostPlan *out)
+fof_status make_plan_on(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx,
+                        int32_t n_boxes, bool refine, HostPlan *out)
 {
     if (!offsets || !box || !lx || n_boxes < 1) return FOF_ERR_INVALID_ARG;
     if (offsets[0] != 0) return FOF_ERR_INVALID_ARG;
@@ -374,7 +399,7 @@ fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box
         const int64_t nb = offsets[k + 1] - offsets[k];
         if (nb < 0 || offsets[k + 1] > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
         BoxDev &b = p.boxes[(size_t)k];
-        fof_status st = box_geometry(c->opt, nb, box[k], lx[k], cells, &b);
+        fof_status st = box_geometry(c->opt, nb, box[k], lx[k], cells, refine, &b);
         if (st != FOF_OK) return st;
         b.p0 = offsets[k];
         b.p1 = offsets[k + 1];
@@ -386,6 +411,24 @@ fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box
     fof_status st = make_layout(c->opt, offsets[n_boxes], cells, n_boxes, &p);
     if (st != FOF_OK) return st;
     *out = std::move(p);
+    return FOF_OK;
+}
+
+// The plan of a run in a workspace of `bytes` bytes. Every request is judged
+// by the cells the options ask for; their subdivision is taken where its
+// cells are within the limits and the workspace holds it. `need`: the larger
+// of the two sizes, so a workspace of that size serves either.
+fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx, int32_t n_boxes,
+                     size_t bytes, HostPlan *out, size_t *need)
+{
+    fof_status st = make_plan_on(c, offsets, box, lx, n_boxes, false, out);
+    if (st != FOF_OK) return st;
+    *need = out->total;
+    if (c->opt.cell_factor > 0.0) return FOF_OK;
+    HostPlan fine;
+    if (make_plan_on(c, offsets, box, lx, n_boxes, true, &fine) != FOF_OK) return FOF_OK;
+    if (fine.total > *need) *need = fine.total;
+    if (fine.total <= bytes) *out = std::move(fine);
     return FOF_OK;
 }
 
@@ -541,7 +584,8 @@ fof_status do_build(fof_ctx *c, const float *d_pos, const int64_t *off, const do
         if (!c->timer || !c->timer->init()) return FOF_ERR_DEVICE;
     }
     HostPlan np;
-    fof_status st = make_plan(c, off, box, lx, n_boxes, &np);
+    size_t need = 0;
+    fof_status st = make_plan(c, off, box, lx, n_boxes, c->ws_bytes, &np, &need);
     if (st != FOF_OK) return st;
     if (!d_pos && np.n > 0) return FOF_ERR_INVALID_ARG;
     st = install_plan(c, std::move(np));
@@ -586,13 +630,23 @@ fof_status plan_one_box(const fof_options &o, int64_t n, double box, double lx, 
     if (!options_valid(o)) return FOF_ERR_INVALID_ARG;
     if (n < 0 || n > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
     BoxDev b;
-    fof_status st = box_geometry(o, n, box, lx, 0, &b);
+    fof_status st = box_geometry(o, n, box, lx, 0, false, &b);
     if (st != FOF_OK) return st;
-    b.p0 = 0;
-    b.p1 = n;
     Layout lay;
     st = make_layout(o, n, (int64_t)b.nc * b.nc * b.nc, 1, &lay);
     if (st != FOF_OK) return st;
+    if (o.cell_factor == 0.0) {   // the subdivided cells, where they fit
+        BoxDev fine_box;
+        Layout fine;
+        if (box_geometry(o, n, box, lx, 0, true, &fine_box) == FOF_OK &&
+            make_layout(o, n, (int64_t)fine_box.nc * fine_box.nc * fine_box.nc, 1, &fine) == FOF_OK &&
+            fine.total <= bytes) {
+            b = fine_box;
+            lay = fine;
+        }
+    }
+    b.p0 = 0;
+    b.p1 = n;
     *need = lay.total;
     if (lay.total > bytes) return FOF_OK;
     carve(o, lay, b, ws, out);
@@ -638,9 +692,10 @@ fof_status fof_workspace_bytes(fof_ctx *ctx, const int64_t *h_box_offsets, const
 {
     if (!ctx || !bytes) return FOF_ERR_INVALID_ARG;
     HostPlan p;
-    fof_status st = make_plan(ctx, h_box_offsets, h_box, h_lx, n_boxes, &p);
+    size_t need = 0;
+    fof_status st = make_plan(ctx, h_box_offsets, h_box, h_lx, n_boxes, 0, &p, &need);
     if (st != FOF_OK) return st;
-    *bytes = p.total;
+    *bytes = need;
     return FOF_OK;
 }
 
