@@ -85,7 +85,8 @@ typedef struct {
     int32_t collect_stats;   /* 1: count pair tests, links, band hits, CAS retries (slower) */
     int32_t dense_min;       /* cells holding at least this many particles are searched by whole
                                 wavefronts (64 particles against broadcast candidates); the others
-                                per particle. 0 = default (32) */
+                                per particle. 0 = default (32; 8 where the search subdivides
+                                automatic cells) */
     int32_t collect_timings; /* 1: record HIP events around every kernel launch on the context's
                                 stream (read with fof_get_kernel_times) */
     int32_t sort_segment_log2; /* the cell sort takes 2^k consecutive cells per work-group (their

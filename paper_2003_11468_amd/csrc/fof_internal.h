@@ -103,7 +103,8 @@ struct Plan {
     int32_t *gmin;          // [n] smallest original index of the group, at its root
     int32_t *parent;        // [n] union-find forest over sorted indices
     int32_t *gsize;         // [n] group member count at roots (sorted indices)
-    int4 *items;            // [max_items] dense work: {cx | cy << 16, first home particle, box, cz}
+    int4 *items;            // [max_items] dense work: {first home particle, particles from it to the
+                            // cell's end | kItemFirst for the cell's first item, box, 0}
     int2 *edges;            // [max_edges] linked pairs found by the sparse search
     int2 *bnd;              // domain mode: [max_edges] linked pairs across domains, then their root pairs
     unsigned int *edge_fill;   // [kEdgeSlices] pairs appended to each slice (may exceed its capacity)
@@ -126,6 +127,14 @@ constexpr int kSegLog2Max = 16;
 constexpr int kSegLog2Auto = 16;      // largest segment the automatic choice takes
 constexpr int kSegTarget = 1365;      // default: about this many particles per segment
 constexpr int kMaxSubLog2 = 10;
+
+constexpr int kItemFirst = INT32_MIN;   // the sign bit: counts stay below 2^31
+
+// What the pre-merge leaves in the w of a dense cell's first sorted position
+// (the cell sort leaves 0): all particles are in one group; every link inside
+// the cell has been merged.
+constexpr int kCellOneGroup = 1;
+constexpr int kCellJoined = 2;
 
 // Capacity of the dense work-item list (fof_link.hip).
 int64_t max_dense_items(int64_t n, int dense_min);

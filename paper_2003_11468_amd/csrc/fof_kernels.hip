@@ -378,6 +378,8 @@ constexpr int kSegWaves = kSegBlock / 64;
 constexpr int kSegUnroll = 4;            // particles in flight per thread
 constexpr int kOrderCap = 4080;          // segments up to this many particles are placed through LDS
 constexpr int kCntCap = 4080;            // occupied cells counted at once (a window of ranks)
+constexpr int kDenseWords = kOrderCap / 64 + 2;   // 64-slot masks a segment placed through LDS can touch
+static_assert(kDenseWords * 4 <= kOrderCap, "the masks fit where the slot order goes");
 static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window");
 
 // One work-group per segment of 2^seg_shift consecutive cells, whose P
@@ -397,9 +399,8 @@ static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window"
 // occupied cells than that):
 //  3. particle count per occupied cell, indexed by rank;
 //  4. exclusive prefix over the occupied cells (thread t owns a run);
-//  5. cell starts out, and dense link work items {cx | cy << 16, first home
-//     particle, box, cz}, one per 64 particles of every cell with at least dense_min
-//     particles (the cell of a rank is found from the rank bases);
+//  5. cell starts out, and dense link work items (Plan::items), one per 64
+//     particles of every cell with at least dense_min particles (the cell of a rank is found from the rank bases);
 //  6. place the particles: the LDS cursors give each its slot; up to
 //     kOrderCap particles the slot order is kept in LDS and the outputs are
 //     written in slot order (coalesced), otherwise written directly.
@@ -408,26 +409,6 @@ static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window"
 // kWordsMax: the occupancy words of the largest segment this instance takes
 // (segments of up to 2^14 cells: one word per thread, the smaller LDS
 // footprint; above: several per thread).
-// Position of the t-th lowest set bit of m (t < popcount(m)), by halving the
-// window with population counts.
-__device__ __forceinline__ int nth_bit(unsigned m, int t)
-{
-    int pos = 0;
-#pragma unroll
-    for (int w = 16; w > 0; w >>= 1) {
-        const unsigned low = m & ((1u << w) - 1u);
-        const int c = __popc(low);
-        if (t >= c) {
-            t -= c;
-            m >>= w;
-            pos += w;
-        } else {
-            m = low;
-        }
-    }
-    return pos;
-}
-
 template <int kWordsMax>
 __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(kWordsMax <= 1024 ? 8 : 6))) k_cell_sort(Plan p)
 {
@@ -437,10 +418,10 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
     __shared__ int cnt[kCntCap];                     // per occupied cell of a window: count, start, cursor
     __shared__ unsigned bits[kWordsMax];             // occupancy of the segment's cells
     __shared__ int wbase[kWordsMax];                 // occupied cells before each word
-    __shared__ unsigned short order[kOrderCap];
+    __shared__ __align__(8) unsigned short order[kOrderCap];
     __shared__ unsigned short lrank[kOrderCap];      // per particle (P <= kOrderCap): its cell, then the cell's rank
     __shared__ int lds[kSegWaves];
-    __shared__ int occ_total;
+    __shared__ int occ_total, item_base;
     const int j = (int)blockIdx.x;
     const int words = 1 << (p.seg_shift - 5);
     const int64_t cell0 = (int64_t)j << p.seg_shift;
@@ -450,6 +431,8 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
     const int tid = (int)threadIdx.x;
     const bool through_lds = P <= kOrderCap;
     const int seg_cells = words << 5;
+    // dense slots of a segment placed through LDS (step 5), before its slot order (step 6)
+    unsigned long long *dense = reinterpret_cast<unsigned long long *>(order);
     bool bad = false;
     // the segment's cell of a staged particle; a cell outside the segment
     // cannot happen with a consistent partition and is latched, not used
@@ -517,6 +500,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
     for (int r0 = 0; r0 < n_occ; r0 += kCntCap) {
         const int nw = min(kCntCap, n_occ - r0);
         for (int k = tid; k < nw; k += kSegBlock) cnt[k] = 0;
+        if (tid == 0) item_base = -1;   // no dense cell in this window so far
         __syncthreads();
 
         // 3. particles per occupied cell of the window
@@ -560,55 +544,59 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         }
         __syncthreads();
 
-        // 5. cell starts, dense work items
+        // 5. cell starts, dense work items: the segment takes its items' places
+        // with one atomic per window (one per wave had every work-group of the
+        // grid queue at that counter), and the dense masks of a segment placed
+        // through LDS are gathered there first (only its first and last mask
+        // words are shared with other segments)
         {
-            const int lane = lane_id();
-            for (int kb = 0; kb < nw; kb += kSegBlock) {
-                const int k = kb + tid;
-                int v = 0, start = 0;
-                if (k < nw) {
+            int chunks = 0;   // items of this thread's cells
+#pragma unroll 1
+            for (int k = tid; k < nw; k += kSegBlock) {
+                const int st = cnt[k];
+                const int v = (k + 1 < nw ? cnt[k + 1] : slot0 + total) - st;
+                p.cstart[a + r0 + k] = a + st;
+                chunks += v >= p.dense_min ? (v + 63) >> 6 : 0;
+            }
+            if (chunks) item_base = 0;
+            __syncthreads();
+            if (item_base >= 0) {
+                int n_items;
+                int slot = block_excl_scan<kSegBlock>(chunks, lds, &n_items);
+                if (through_lds)
+                    for (int w = tid; w < kDenseWords; w += kSegBlock) dense[w] = 0ull;
+                if (tid == 0) item_base = (int)atomicAdd(&p.counters->n_items, (unsigned)n_items);
+                __syncthreads();
+                slot += item_base;
+                const int mask0 = a >> 6;
+#pragma unroll 1
+                for (int k = tid; k < nw && chunks; k += kSegBlock) {
                     const int st = cnt[k];
-                    v = (k + 1 < nw ? cnt[k + 1] : slot0 + total) - st;
-                    start = a + st;
-                    p.cstart[a + r0 + k] = start;
+                    const int v = (k + 1 < nw ? cnt[k + 1] : slot0 + total) - st;
+                    if (v < p.dense_min) continue;
+                    const int start = a + st;
+                    // the segment's box, kept from step 1, unless the cell lies in another
+                    const int bx = p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, start, hint);
+                    for (int q = 0; q < v; q += 64, ++slot)
+                        if (slot < p.max_items)
+                            p.items[slot] = make_int4(start + q, (v - q) | (q ? 0 : kItemFirst), bx, 0);
+                    // the cell's slots, in the masks by which the per-particle search skips dense tiles
+                    for (int s0 = start; s0 < start + v;) {
+                        const int l0 = s0 & 63, l1 = min(64, l0 + (start + v - s0));
+                        const unsigned long long m = (l1 == 64 ? ~0ull : (1ull << l1) - 1ull) & ~((1ull << l0) - 1ull);
+                        if (through_lds) atomicOr(&dense[(s0 >> 6) - mask0], m);
+                        else atomicOr(&p.tile_dense[s0 >> 6], m);
+                        s0 += l1 - l0;
+                    }
                 }
-                const int chunks = (k < nw && v >= p.dense_min) ? (v + 63) >> 6 : 0;
-                if (__ballot(chunks > 0)) {
-                    const int cincl = wave_incl_scan(chunks);
-                    const int wave_items = __shfl(cincl, 63, 64);
-                    int slot = 0;
-                    if (lane == 63) slot = (int)atomicAdd(&p.counters->n_items, (unsigned)wave_items);
-                    slot = __shfl(slot, 63, 64) + cincl - chunks;
-                    if (chunks) {
-                        // the word holding rank r0 + k: the last one whose base is at most that
-                        const int rk = r0 + k;
-                        int lo = 0, hi = words - 1;
-                        while (lo < hi) {
-                            const int mid = (lo + hi + 1) >> 1;
-                            if (wbase[mid] <= rk) lo = mid;
-                            else hi = mid - 1;
-                        }
-                        const int64_t gc = cell0 + (lo << 5) + nth_bit(bits[lo], rk - wbase[lo]);
-                        // the segment's box, kept from step 1, unless the cell lies in another
-                        const int bx = p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, start, hint);
-                        // the cell's coordinates in its box: local < nc^3 <= 2^33 and the
-                        // divisors are below 2^22, so the double quotients truncate exactly
-                        const BoxDev &bd = box_of(p, bx);
-                        const int nc = bd.nc;
-                        const int64_t local = gc - bd.cell_base, nc2 = (int64_t)nc * nc;
-                        const int cz = (int)((double)local / (double)nc2);
-                        const int rem = (int)(local - cz * nc2);
-                        const int cy = (int)((double)rem / (double)nc);
-                        const int cx = rem - cy * nc;
-                        for (int q = 0; q < v; q += 64, ++slot)
-                            if (slot < p.max_items) p.items[slot] = make_int4(cx | (cy << 16), start + q, bx, cz);
-                        // the cell's slots, in the masks by which the per-particle search skips dense tiles
-                        for (int s0 = start; s0 < start + v;) {
-                            const int lo = s0 & 63, hi = min(64, lo + (start + v - s0));
-                            const unsigned long long m = (hi == 64 ? ~0ull : (1ull << hi) - 1ull) & ~((1ull << lo) - 1ull);
-                            atomicOr(&p.tile_dense[s0 >> 6], m);
-                            s0 += hi - lo;
-                        }
+                if (through_lds) {
+                    __syncthreads();
+                    const int last = (e - 1) >> 6;
+                    for (int w = mask0 + tid; w <= last; w += kSegBlock) {
+                        const unsigned long long m = dense[w - mask0];
+                        if (!m) continue;
+                        if (w == mask0 || w == last) atomicOr(&p.tile_dense[w], m);
+                        else p.tile_dense[w] = m;
                     }
                 }
             }

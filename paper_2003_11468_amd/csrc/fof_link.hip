@@ -41,6 +41,11 @@ using namespace dev;
 
 constexpr int kWaves = kBlock / 64;
 
+__device__ __forceinline__ float lane0(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
 __device__ __forceinline__ float qnan() { return __builtin_nanf(""); }
 
 // Merge the groups that contain roots-or-members a and b; returns a node of the
@@ -1007,6 +1012,8 @@ __device__ __forceinline__ void dense_ranges(const Plan &p, const BoxRegs &br, t
     __builtin_amdgcn_wave_barrier();   // rl and the stage are reused by the next call
 }
 
+constexpr int kDenseSample = 16;   // particles of a large one-group neighbour searched first
+
 template <bool kFP64, bool kStats, bool kGeneral>
 __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
 {
@@ -1022,10 +1029,17 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
     const XcdRange xr = xcd_range(n_items, kWaves, wid);   // items come in cell order
     for (int64_t it = xr.first; it < xr.end; it += xr.stride) {
         const int4 item = p.items[it];
-        const int cxy = __builtin_amdgcn_readfirstlane(item.x);
-        const int first = __builtin_amdgcn_readfirstlane(item.y);
+        const int first = __builtin_amdgcn_readfirstlane(item.x);
+        const int rem = __builtin_amdgcn_readfirstlane(item.y) & ~kItemFirst;
+        const int ce = first + rem;   // end of the cell
+        const int n_home = min(64, rem);
+        // home particles per copy (H) and copies (G = 64 / H)
+        const int H = n_home > 32 ? 64 : (n_home > 16 ? 32 : 16);
+        const int G = 64 / H, q = lane / H;
+        const int i = first + (lane & (H - 1));
+        const bool vi = i < ce;
+        const float4 pi = vi ? p.sorted[i] : make_float4(qnan(), qnan(), qnan(), 0.f);
         const int b = __builtin_amdgcn_readfirstlane(item.z);
-        const int cx = cxy & 0xffff, cy = cxy >> 16, cz = __builtin_amdgcn_readfirstlane(item.w);
         const BoxDev &bd = box_of(p, b);
         const int nc = bd.nc;
         const int64_t cb = bd.cell_base;
@@ -1037,6 +1051,11 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
         br.hi32 = bd.hi32;
         br.L32 = bd.L32;
         br.strict = p.strict != 0;
+        // the cell, from its first home particle (lane 0)
+        const int cx = cell_coord(lane0(pi.x), bd.inv_h, nc);
+        const int cy = cell_coord(lane0(pi.y), bd.inv_h, nc);
+        const int cz = cell_coord(lane0(pi.z), bd.inv_h, nc);
+        int root_i = vi ? find_root(p.parent, i, p.find_mode, kGeneral && p.link_random) : -1;
         // the 27 neighbour cells, one per lane (lanes 0-26, neighbour
         // nb = 9 (dz + 1) + 3 (dy + 1) + dx + 1), looked up at once; code:
         // per axis 1 = the neighbour is the top cell across the low face,
@@ -1051,31 +1070,57 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
             nb_j0 = sp.x;
             nb_j1 = sp.y;
         }
-        const int ce = __shfl(nb_j1, 13, 64);   // the cell itself
-        const int n_home = min(64, ce - first);
-        // home particles per copy (H) and copies (G = 64 / H)
-        const int H = n_home > 32 ? 64 : (n_home > 16 ? 32 : 16);
-        const int G = 64 / H, q = lane / H;
-        const int i = first + (lane & (H - 1));
-        const bool vi = i < ce;
-        const float4 pi = vi ? p.sorted[i] : make_float4(qnan(), qnan(), qnan(), 0.f);
-        int root_i = vi ? find_root(p.parent, i, p.find_mode, kGeneral && p.link_random) : -1;
         int known0 = -3, known1 = -3;   // never a node
         // neighbours searched from here: the upper half shell, and the lower
         // half where the neighbour is sparse (a dense one searches the pair)
         const int nlen = nb_j1 - nb_j0;
-        const bool searched = lane < 27 && lane != 13 && nlen > 0 && (lane > 13 || nlen < p.dense_min);
+        bool searched = lane < 27 && lane != 13 && nlen > 0 && (lane > 13 || nlen < p.dense_min);
+        int joined = 0;   // what the pre-merge has done: the home cell's flags
+        bool one_group = false;   // this lane's neighbour is a dense cell found to be one group
+        if constexpr (!kStats) {
+            // A dense cell found to be one group leaves nothing to link when
+            // its group is the home particles' (all of one group themselves):
+            // inside a halo that is nearly every neighbour, and the item ends
+            // here instead of staging all their particles.
+            const bool flagged = lane < 27 && (lane == 13 || (searched && nlen >= p.dense_min));
+            const int fl = flagged ? __float_as_int(p.sorted[nb_j0].w) : 0;
+            joined = __builtin_amdgcn_readlane(fl, 13);
+            const int rh = __builtin_amdgcn_readfirstlane(root_i);   // lane 0 is a home particle
+            one_group = searched && (fl & kCellOneGroup);
+            if (__ballot(vi && root_i != rh) == 0 && one_group)
+                searched = find_root(p.parent, nb_j0, p.find_mode, kGeneral && p.link_random) != rh;
+        }
         const bool home_shift = (code & 0x2a) != 0;   // some axis has code 2
         const bool together = searched && (kFP64 || !home_shift);
 
-        // the cell itself
-        dense_ranges<kFP64, kStats, kGeneral, true>(p, br, st, rl, lane == 13 ? ce - first : 0, first, 0, G, q, i, vi,
-                                                    pi, pi.x, pi.y, pi.z, n_home, root_i, known0, known1, tests, links,
-                                                    band, retries);
-        // every neighbour that needs no shift of the home coordinate, at once
-        dense_ranges<kFP64, kStats, kGeneral, false>(p, br, st, rl, together ? nlen : 0, nb_j0, code, G, q, i, vi,
-                                                     pi, pi.x, pi.y, pi.z, n_home, root_i, known0, known1, tests,
-                                                     links, band, retries);
+        // the cell itself, unless the pre-merge has linked it whole
+        if (!(joined & kCellJoined))
+            dense_ranges<kFP64, kStats, kGeneral, true>(p, br, st, rl, lane == 13 ? ce - first : 0, first, 0, G, q, i,
+                                                        vi, pi, pi.x, pi.y, pi.z, n_home, root_i, known0, known1,
+                                                        tests, links, band, retries);
+        // Every neighbour that needs no shift of the home coordinate, at once;
+        // of a large cell that is one group only the first kDenseSample
+        // particles (they are in no particular order): one link joins the two
+        // cells, and the rest of it is searched after that only if none of
+        // these linked.
+        const bool large = together && one_group && nlen > 2 * kDenseSample;
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+            int j0 = nb_j0, len = together ? (large ? kDenseSample : nlen) : 0;
+            if (pass == 1) {
+                if (__ballot(large) == 0) break;
+                if (vi) root_i = find_root(p.parent, root_i, p.find_mode, kGeneral && p.link_random);
+                const int rh = __builtin_amdgcn_readfirstlane(root_i);
+                bool rest = large;
+                if (__ballot(vi && root_i != rh) == 0 && large)
+                    rest = find_root(p.parent, nb_j0, p.find_mode, kGeneral && p.link_random) != rh;
+                j0 = nb_j0 + kDenseSample;
+                len = rest ? nlen - kDenseSample : 0;
+            }
+            dense_ranges<kFP64, kStats, kGeneral, false>(p, br, st, rl, len, j0, code, G, q, i, vi, pi, pi.x, pi.y,
+                                                         pi.z, n_home, root_i, known0, known1, tests, links, band,
+                                                         retries);
+        }
         if constexpr (!kFP64) {
             // neighbours across a high face, one at a time
             unsigned long long rest = __ballot(searched && !together);
@@ -1105,9 +1150,17 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
     }
 }
 
-// Pre-merge of dense cells (before the pair search): one wavefront per dense
-// cell splits it into k^3 sub-cells small enough that any two particles of
-// one sub-cell are linked. When the sub-cells are smaller still (sub_adj:
+// Pre-merge of dense cells (before the pair search), one wavefront per dense
+// cell. A cell of at most 64 particles is linked whole in registers
+// (cell_rows, close_rows), so the pair search has nothing left to do inside
+// it; cells found to be one group are marked, and the pair search passes over
+// marked neighbours of the home particles' own group. Both kernels are bound
+// by the latency of their dependent loads, so what counts is how few an item
+// needs: on 256 boxes of 1e3 to 1e6 particles (232k items) the pair search
+// went from 1.58 to 1.10 ms and the pre-merge from 0.44 to 0.39 ms; on 1e5
+// particles, where a few halo cores were the tail, the search from 157 to 54
+// us. A larger cell is split into k^3 sub-cells small enough that any two
+// particles of one sub-cell are linked. When the sub-cells are smaller still (sub_adj:
 // any two particles of two sub-cells that touch, across a face, an edge or a
 // corner, are linked), a union-find over the occupied sub-cells in LDS joins
 // every two touching occupied sub-cells. Every particle is then hooked
@@ -1132,6 +1185,56 @@ __device__ __forceinline__ void sub_xyz(int t, int k, float inv_k, float inv_k2,
     sx = r - sy * k;
 }
 
+// Links of each lane's particle with particles j0 .. j1 - 1 of the wave's n
+// (read with readlane): bit j - j0 of the result. kExact: decided in double;
+// else in FP32, `band` set when a result lies in the guard band.
+template <bool kExact>
+__device__ __forceinline__ unsigned cell_row_word(const BoxDev &bd, int j0, int j1, bool strict, float x, float y,
+                                                  float z, bool &band)
+{
+    unsigned w = 0u;
+    for (int j = j0; j < j1; ++j) {
+        const float xj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
+        const float yj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), j));
+        const float zj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), j));
+        bool link;
+        if constexpr (kExact) {
+            link = link_fp64(x, y, z, xj, yj, zj, bd.L, bd.half, bd.l2, strict);
+        } else {
+            const float dx = x - xj, dy = y - yj, dz = z - zj;
+            const float rr = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+            link = rr < bd.lo32;
+            band = band | (!(rr < bd.lo32) & !(rr > bd.hi32));
+        }
+        w |= link ? 1u << (j - j0) : 0u;
+    }
+    return w;
+}
+
+// Links among the n <= 64 particles of one cell, one per lane: bit v of lane
+// u's row is set when u and v are linked (or u == v). About 12 vector
+// instructions per particle and no memory access; a result in the FP32 guard
+// band (rare) has the whole cell decided in double. The differences of a pair
+// are exact negatives either way round, so the rows are symmetric.
+template <bool kFP64>
+__device__ __forceinline__ unsigned long long cell_rows(const BoxDev &bd, int n, bool strict, float x, float y,
+                                                        float z)
+{
+    const int n0 = min(n, 32);
+    unsigned lo = 0u, hi = 0u;
+    bool band = kFP64;
+    if constexpr (!kFP64) {
+        lo = cell_row_word<false>(bd, 0, n0, strict, x, y, z, band);
+        hi = cell_row_word<false>(bd, 32, n, strict, x, y, z, band);
+    }
+    if (__ballot(band & (lane_id() < n))) {
+        lo = cell_row_word<true>(bd, 0, n0, strict, x, y, z, band);
+        hi = cell_row_word<true>(bd, 32, n, strict, x, y, z, band);
+    }
+    return ((((unsigned long long)hi) << 32) | lo) | (1ull << lane_id());
+}
+
+template <bool kFP64>
 __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
 {
     // per sub-cell: (hooking key << 32 | particle) of its first particle, ~0 when empty
@@ -1148,20 +1251,45 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
     const XcdRange xr = xcd_range(n_items, kWaves, wid);
     for (int64_t it = xr.first; it < xr.end; it += xr.stride) {
         const int4 item = p.items[it];
-        const int cxy = __builtin_amdgcn_readfirstlane(item.x);
-        const int first = __builtin_amdgcn_readfirstlane(item.y);
+        const int cs = __builtin_amdgcn_readfirstlane(item.x);
+        const int tail = __builtin_amdgcn_readfirstlane(item.y);
+        if (!(tail & kItemFirst)) continue;   // the cell's first item does the whole cell
+        const int count = tail & ~kItemFirst;
         const int b = __builtin_amdgcn_readfirstlane(item.z);
-        const int cx = cxy & 0xffff, cy = cxy >> 16, cz = __builtin_amdgcn_readfirstlane(item.w);
         const BoxDev &bd = box_of(p, b);
-        const int nc = bd.nc;
-        const int2 sp = cell_span(p, bd.cell_base + ((int64_t)cz * nc + cy) * nc + cx);
-        const int cs = __builtin_amdgcn_readfirstlane(sp.x);
-        if (first != cs) continue;   // the cell's first item does the whole cell
+        if (count <= 64) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (lane < count) v = p.sorted[cs + lane];
+            const unsigned long long row =
+                close_rows(cell_rows<kFP64>(bd, count, p.strict != 0, v.x, v.y, v.z), ~0ull >> (64 - count));
+            int r = cs + __ffsll((long long)row) - 1;   // smallest index of the group
+            if (rnd) {   // smallest hooking key instead, by the group's lowest lane
+                const int at = r - cs;
+                rp[lane] = kEmpty;
+                __builtin_amdgcn_wave_barrier();
+                if (lane < count) atomicMin(&rp[at], ((unsigned long long)link_key(cs + lane, true) << 32) |
+                                                         (unsigned)(cs + lane));
+                __builtin_amdgcn_wave_barrier();
+                r = (int)(unsigned)(rp[at] & 0xffffffffull);
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (lane < count && r != cs + lane) p.parent[cs + lane] = r;
+            const bool one = __ballot(lane < count && !(row & 1ull)) == 0;
+            if (lane == 0) p.sorted[cs].w = __int_as_float(kCellJoined | (one ? kCellOneGroup : 0));
+            continue;
+        }
         const int k = bd.sub_k;
-        if (k == 0) continue;
+        if (k == 0) {
+            if (lane == 0) p.sorted[cs].w = 0.f;
+            continue;
+        }
         const bool adj = bd.sub_adj != 0;
         const float inv_k = 1.0f / (float)k, inv_k2 = 1.0f / (float)(k * k);
-        const int ce = __builtin_amdgcn_readfirstlane(sp.y);
+        const int ce = cs + count;
+        bool one = false;   // all joined into one set
+        const float4 p0 = p.sorted[cs];   // the cell, from its first particle
+        const int cx = cell_coord(p0.x, bd.inv_h, bd.nc), cy = cell_coord(p0.y, bd.inv_h, bd.nc),
+                  cz = cell_coord(p0.z, bd.inv_h, bd.nc);
         const int nsub = k * k * k;
         for (int t = lane; t < nsub; t += 64) {
             rp[t] = kEmpty;
@@ -1222,6 +1350,7 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
                     }
                 }
                 row = close_rows(row, __ballot(lane < n_used && row != (1ull << lane)));
+                one = __ballot(lane < n_used && !(row & 1ull)) == 0;
                 __builtin_amdgcn_wave_barrier();   // every map entry read
                 if (lane < n_used) {
                     const int rt = ul[__ffsll((long long)row) - 1];
@@ -1242,11 +1371,15 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
                 }
                 __builtin_amdgcn_wave_barrier();
                 // the particle of smallest key of each joined set, at its root sub-cell
+                const int r0 = lds_find(jf, ul[0]);
+                bool same = true;
                 for (int q = lane; q < n_used; q += 64) {
                     const int t = ul[q];
                     const int r = lds_find(jf, t);
+                    same = same && r == r0;
                     if (r != t) atomicMin(&rp[r], rp[t]);
                 }
+                one = __ballot(!same) == 0;
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -1255,6 +1388,7 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
             const int r = (int)(unsigned)(rp[adj ? lds_find(jf, sj) : sj] & 0xffffffffull);
             if (r != j) p.parent[j] = r;   // a key smaller than j's: a valid hook of a root
         }
+        if (lane == 0) p.sorted[cs].w = __int_as_float(one ? kCellJoined | kCellOneGroup : 0);
         __builtin_amdgcn_wave_barrier();
     }
 }
@@ -1533,7 +1667,7 @@ hipError_t launch_link_t(const Plan &p, hipStream_t stream, KernelTimer *t, cons
         hipError_t e = hipEventRecord(fk->fork, stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(fk->side, fk->fork, 0);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_dense_premerge, dim3((unsigned)p.dense_blocks), dim3(kBlock), 0, fk->side, p);
+        hipLaunchKernelGGL((k_dense_premerge<kFP64>), dim3((unsigned)p.dense_blocks), dim3(kBlock), 0, fk->side, p);
         e = hipEventRecord(fk->join, fk->side);
         if (e != hipSuccess) return e;
     }
@@ -1545,7 +1679,7 @@ hipError_t launch_link_t(const Plan &p, hipStream_t stream, KernelTimer *t, cons
         if (e != hipSuccess) return e;
     } else if (premerge) {
         if (t) t->mark(K_PREMERGE, false, stream);
-        hipLaunchKernelGGL(k_dense_premerge, dim3((unsigned)p.dense_blocks), dim3(kBlock), 0, stream, p);
+        hipLaunchKernelGGL((k_dense_premerge<kFP64>), dim3((unsigned)p.dense_blocks), dim3(kBlock), 0, stream, p);
         if (t) t->mark(K_PREMERGE, true, stream);
     }
     if (t) t->mark(K_LINK_DENSE, false, stream);
