@@ -51,6 +51,9 @@ struct Layout {
     int64_t n_cells = 0;
     int64_t scan_tiles = 0;
     int64_t n_tiles = 0;
+    int32_t levels = 2, direct = 0, fused_link = 0;
+    int32_t group_parts = 1;
+    int64_t group_counts = 1;
     int32_t bucket_shift = 0, n_buckets = 1;
     int32_t seg_shift = 0, sub_log2 = 0;
     int64_t n_segments = 0;
@@ -206,14 +209,17 @@ fof_status cells_per_axis(const fof_options &o, int64_t n_box, double L, double 
 // taken as it is.
 constexpr double kRefineSide = 1.375;
 constexpr double kRefineCells = 64.0;
+constexpr double kOneSegmentCells = 40.0;   // per axis: 64000 cells, of the 2^16 a segment holds
 
-int64_t search_cells_per_axis(const fof_options &o, int64_t n_box, double L, double lx, int64_t nc)
+int64_t search_cells_per_axis(const fof_options &o, int64_t n_box, double L, double lx, int64_t nc, bool only_box)
 {
     if (o.cell_factor > 0.0 || n_box < 1) return nc;
     double want = std::floor(L / (kRefineSide * lx));
     const double most = std::floor(std::cbrt(kRefineCells * (double)n_box));
     if (want > most) want = most;
     if (want > kMaxCellsPerAxis) want = kMaxCellsPerAxis;
+    // a run small enough for one segment keeps its cells within one
+    if (only_box && n_box <= fof::kOneSegment && want > kOneSegmentCells) want = kOneSegmentCells;
     return want > (double)nc ? (int64_t)want : nc;
 }
 
@@ -288,13 +294,13 @@ int dense_min_of(const fof_options &o, bool fine)
 // descriptor, cells starting at global cell `cell_base`; `refine`: on the
 // search's own grid (search_cells_per_axis).
 fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, int64_t cell_base, bool refine,
-                        BoxDev *out)
+                        bool only_box, BoxDev *out)
 {
     if (!(L > 0.0) || !std::isfinite(L) || !(l > 0.0) || !std::isfinite(l)) return FOF_ERR_INVALID_ARG;
     int64_t nc = 0;
     fof_status st = cells_per_axis(o, nb, L, l, &nc);
     if (st != FOF_OK) return st;
-    if (refine) nc = search_cells_per_axis(o, nb, L, l, nc);
+    if (refine) nc = search_cells_per_axis(o, nb, L, l, nc, only_box);
     BoxDev &b = *out;
     std::memset(&b, 0, sizeof(b));
     b.cell_base = cell_base;
@@ -307,6 +313,18 @@ fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, in
     sub_cells(L, nc, l, &b.sub_k, &b.sub_adj);
     return FOF_OK;
 }
+
+// Sizes up to which a run is laid out for few launches; each line lies where
+// the two ways measure the same, on uniform and clustered boxes:
+//  one sort level: its tiles take their places by atomics on at most
+//   kWideBuckets counters (14 ns each on one of them);
+//  results straight to input order: scattered writes in outputs that fit the
+//   caches (3e5 particles 9 us against 20 in three launches, 1e6 28 against 27);
+//  fused link: a wave that merges its own links waits for them (1e5 clustered
+//   particles 41 us against 23 + 14 + 25 in three launches).
+constexpr int64_t kOneLevelMax = 1 << 21;
+constexpr int64_t kDirectMax = 1 << 20;
+constexpr int64_t kFusedLinkMax = 1 << 17;
 
 // Sort levels and the workspace carve-up for n particles in `cells` cells
 // over n_boxes boxes.
@@ -336,6 +354,21 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     }
     if (p.seg_shift < p.bucket_shift - fof::kMaxSubLog2) p.seg_shift = p.bucket_shift - fof::kMaxSubLog2;
     if (p.seg_shift > fof::kSegLog2Max) return FOF_ERR_UNSUPPORTED;   // more cells than the levels hold
+    // Fewer levels for fewer segments, so that small runs, whose time is the
+    // launches, need fewer: up to kWideBuckets segments are sorted without
+    // buckets, and up to kOneSegment particles in at most one segment's cells
+    // straight from the input. Per-kernel timers time the general path.
+    if (!o.collect_timings && n_total > 0) {
+        if (n_total <= fof::kOneSegment && cells <= (int64_t)1 << fof::kSegLog2Max && !o.sort_segment_log2) {
+            p.levels = 0;
+            while ((last >> p.seg_shift) > 0) ++p.seg_shift;
+        } else if ((last >> p.seg_shift) < fof::kWideBuckets && n_total <= kOneLevelMax) {
+            p.levels = 1;
+        }
+        if (p.levels < 2) p.bucket_shift = p.seg_shift;
+        p.direct = n_total <= kDirectMax;
+        p.fused_link = n_total <= kFusedLinkMax && !o.collect_stats && o.domains <= 1 && !(o.schedule & (16 | 32));
+    }
     if (p.bucket_shift < p.seg_shift) p.bucket_shift = p.seg_shift;
     p.sub_log2 = p.bucket_shift - p.seg_shift;
     p.n_buckets = (int32_t)((last >> p.bucket_shift) + 1);
@@ -365,7 +398,9 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     p.o_boxes = take(sizeof(BoxDev) * (size_t)n_boxes);
     p.o_p0 = take(sizeof(int64_t) * ((size_t)n_boxes + 1));
     p.o_counters = take(sizeof(Counters));
-    p.o_groups = take(sizeof(unsigned long long) * (size_t)n_boxes);
+    p.group_parts = n_boxes < fof::kGroupParts ? fof::kGroupParts / n_boxes : 1;
+    p.group_counts = p.group_parts > 1 ? (int64_t)n_boxes * p.group_parts * fof::kGroupStride : n_boxes;
+    p.o_groups = take(sizeof(unsigned long long) * (size_t)p.group_counts);
     p.o_cell = take(sizeof(int32_t) * (n + 4));   // starts of the occupied cells (at most n) + sentinels
     p.o_part = take(sizeof(int32_t) * (size_t)p.scan_tiles);
     p.o_kmap = take(sizeof(int32_t) * n);
@@ -382,7 +417,7 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     p.max_edges = (p.max_edges + fof::kEdgeSlices - 1) / fof::kEdgeSlices * fof::kEdgeSlices;
     p.o_edges = take(sizeof(int32_t) * 2 * (size_t)p.max_edges);
     p.o_edge_fill = take(sizeof(uint32_t) * fof::kEdgeSlices);
-    p.o_hist = take(sizeof(int32_t) * ((size_t)p.n_buckets * (size_t)p.n_tiles + 1));
+    p.o_hist = take(sizeof(int32_t) * ((size_t)p.n_buckets * ((size_t)p.n_tiles + 1) + 1));
     p.o_staging = take(sizeof(float) * 4 * n);
     p.o_stpos = take(sizeof(int32_t) * n);
     p.o_wave_roots = take(sizeof(int32_t) * ((n + 63) / 64));
@@ -412,7 +447,7 @@ fof_status make_plan_on(const fof_ctx *c, const int64_t *offsets, const double *
         const int64_t nb = offsets[k + 1] - offsets[k];
         if (nb < 0 || offsets[k + 1] > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
         BoxDev &b = p.boxes[(size_t)k];
-        fof_status st = box_geometry(c->opt, nb, box[k], lx[k], cells, coarse != nullptr, &b);
+        fof_status st = box_geometry(c->opt, nb, box[k], lx[k], cells, coarse != nullptr, n_boxes == 1, &b);
         if (st != FOF_OK) return st;
         b.p0 = offsets[k];
         b.p1 = offsets[k + 1];
@@ -464,6 +499,11 @@ void carve(const fof_options &o, const Layout &p, const BoxDev &box0, void *ws, 
     d.stats = o.collect_stats;
     d.scan_tiles = p.scan_tiles;
     d.n_tiles = p.n_tiles;
+    d.levels = p.levels;
+    d.group_parts = p.group_parts;
+    d.group_counts = p.group_counts;
+    d.direct = p.direct;
+    d.fused_link = p.fused_link;
     d.bucket_shift = p.bucket_shift;
     d.n_buckets = p.n_buckets;
     d.seg_shift = p.seg_shift;
@@ -508,6 +548,8 @@ void carve(const fof_options &o, const Layout &p, const BoxDev &box0, void *ws, 
     d.seg_end = at<int32_t>(ws, p.o_seg);
     d.staging2 = at<float4>(ws, p.o_staging2);
     d.stage2_k = at<int32_t>(ws, p.o_stage2_k);
+    d.seg_src = p.levels == 2 ? d.staging2 : d.staging;
+    d.seg_k = p.levels == 2 ? d.stage2_k : nullptr;
     d.edge_fill = at<unsigned int>(ws, p.o_edge_fill);
     d.n_waves = (p.n + 63) / 64;
     d.label = nullptr;
@@ -609,24 +651,22 @@ fof_status do_build(fof_ctx *c, const float *d_pos, const int64_t *off, const do
 
 fof_status enqueue_build(fof_ctx *c, hipStream_t s)
 {
-    hipError_t e = fof::launch_clear(c->dev, s, c->timer);
-    if (e == hipSuccess) e = fof::launch_build(c->dev, s, c->timer);
-    return dev_err(e);
+    return dev_err(fof::launch_build(c->dev, s, c->timer));
 }
 
 fof_status read_back(fof_ctx *c, int64_t *h_n_groups, Counters *h_counters)
 {
     const HostPlan &p = c->plan;
-    std::vector<unsigned long long> g((size_t)p.n_boxes);
-    Counters cnt{};
-    if (hipMemcpyAsync(g.data(), c->dev.n_groups, sizeof(unsigned long long) * g.size(), hipMemcpyDeviceToHost,
-                       c->stream) != hipSuccess)
-        return FOF_ERR_DEVICE;
-    if (hipMemcpyAsync(&cnt, c->dev.counters, sizeof(Counters), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+    // the counters and, behind them in the workspace, the group counts: one copy
+    const size_t bytes = (p.o_groups - p.o_counters) + sizeof(unsigned long long) * (size_t)p.group_counts;
+    std::vector<char> buf(bytes);
+    if (hipMemcpyAsync(buf.data(), c->dev.counters, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
         return FOF_ERR_DEVICE;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return FOF_ERR_DEVICE;
+    Counters cnt;
+    std::memcpy(&cnt, buf.data(), sizeof(cnt));
     if (h_n_groups)
-        for (size_t k = 0; k < g.size(); ++k) h_n_groups[k] = (int64_t)g[k];
+        for (int32_t k = 0; k < p.n_boxes; ++k) h_n_groups[k] = fof::groups_of_box(buf.data() + (p.o_groups - p.o_counters), c->dev, k);
     if (h_counters) *h_counters = cnt;
     if (cnt.error & 2u) return FOF_ERR_DEVICE;   // a device-side consistency check failed
     return (cnt.error & 1u) ? FOF_ERR_OUT_OF_BOX : FOF_OK;
@@ -636,6 +676,15 @@ fof_status read_back(fof_ctx *c, int64_t *h_n_groups, Counters *h_counters)
 
 namespace fof {
 
+int64_t groups_of_box(const void *counts, const Plan &p, int32_t b)
+{
+    const unsigned long long *g = static_cast<const unsigned long long *>(counts);
+    if (p.group_parts == 1) return (int64_t)g[b];
+    unsigned long long sum = 0;
+    for (int q = 0; q < p.group_parts; ++q) sum += g[((int64_t)b * p.group_parts + q) * kGroupStride];
+    return (int64_t)sum;
+}
+
 fof_status plan_one_box(const fof_options &o, int64_t n, double box, double lx, void *ws, size_t bytes, Plan *out,
                         size_t *need)
 {
@@ -643,7 +692,7 @@ fof_status plan_one_box(const fof_options &o, int64_t n, double box, double lx, 
     if (!options_valid(o)) return FOF_ERR_INVALID_ARG;
     if (n < 0 || n > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
     BoxDev b;
-    fof_status st = box_geometry(o, n, box, lx, 0, false, &b);
+    fof_status st = box_geometry(o, n, box, lx, 0, false, true, &b);
     if (st != FOF_OK) return st;
     Layout lay;
     st = make_layout(o, n, (int64_t)b.nc * b.nc * b.nc, 1, false, &lay);
@@ -651,7 +700,7 @@ fof_status plan_one_box(const fof_options &o, int64_t n, double box, double lx, 
     if (o.cell_factor == 0.0) {   // the subdivided cells, where they fit
         BoxDev fine_box;
         Layout fine;
-        if (box_geometry(o, n, box, lx, 0, true, &fine_box) == FOF_OK &&
+        if (box_geometry(o, n, box, lx, 0, true, true, &fine_box) == FOF_OK &&
             fine_box.nc > b.nc &&
             make_layout(o, n, (int64_t)fine_box.nc * fine_box.nc * fine_box.nc, 1, true, &fine) == FOF_OK &&
             fine.total <= bytes) {
@@ -870,8 +919,7 @@ fof_status fof_graph_capture(fof_ctx *ctx, const float *d_pos, const int64_t *h_
     if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         // no per-kernel events inside a graph
-        e = fof::launch_clear(ctx->dev, cs, nullptr);
-        if (e == hipSuccess) e = fof::launch_build(ctx->dev, cs, nullptr);
+        e = fof::launch_build(ctx->dev, cs, nullptr);
         if (e == hipSuccess) e = fof::launch_link(ctx->dev, cs, nullptr, &fk);
         if (e == hipSuccess) e = fof::launch_finalize(ctx->dev, cs, nullptr);
         hipGraph_t g = nullptr;

@@ -386,18 +386,25 @@ inline unsigned xcd_grid(int64_t tiles) { return (unsigned)(((tiles + kXcds - 1)
 
 // Persistent kernels: the waves of XCD x (groups g with g % 8 == x) share the
 // contiguous work range [x * span, (x + 1) * span), span = ceil(total / 8).
-// Call with a grid that is a multiple of 8.
+// Call with a grid (or a part of one: work-group `block` of `blocks`, starting
+// at a multiple of 8) that is a multiple of 8.
 struct XcdRange {
     int64_t first, end, stride;
 };
 
-__device__ __forceinline__ XcdRange xcd_range(int64_t total, int waves_per_group, int wave_in_group)
+__device__ __forceinline__ XcdRange xcd_range(int64_t total, int waves_per_group, int wave_in_group, int block,
+                                              int blocks)
 {
-    const int64_t xcd = blockIdx.x % kXcds, g = blockIdx.x / kXcds, groups = gridDim.x / kXcds;
+    const int64_t xcd = block % kXcds, g = block / kXcds, groups = blocks / kXcds;
     const int64_t span = (total + kXcds - 1) / kXcds;
     const int64_t lo = xcd * span;
     const int64_t hi = lo + span < total ? lo + span : total;
     return {lo + g * waves_per_group + wave_in_group, hi, groups * waves_per_group};
+}
+
+__device__ __forceinline__ XcdRange xcd_range(int64_t total, int waves_per_group, int wave_in_group)
+{
+    return xcd_range(total, waves_per_group, wave_in_group, blockIdx.x, gridDim.x);
 }
 
 __device__ __forceinline__ const BoxDev &box_of(const Plan &p, int b)

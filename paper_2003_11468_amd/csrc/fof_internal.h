@@ -56,8 +56,14 @@ struct Plan {
     int32_t stats;          // 1: count pair tests etc.
     int64_t scan_tiles;     // scratch ints for the tile sums of the scans
     int64_t n_tiles;        // input tiles of the bucket pass (2048 particles each)
+    int32_t levels;         // levels of the sort above the cells: 2 buckets and segments, 1 segments
+                            // alone (bucket = segment), 0 none (one segment, sorted from the input)
+    int32_t group_parts;    // partial group counts per box, kGroupStride entries apart (1: no stride)
+    int64_t group_counts;   // entries of n_groups
+    int32_t direct;         // 1: the results are written straight to input order (no staging slots)
+    int32_t fused_link;     // 1: the per-particle search merges its links itself, beside the pre-merge
     int32_t bucket_shift;   // bucket of a cell = cell >> bucket_shift
-    int32_t n_buckets;      // at most 256
+    int32_t n_buckets;      // at most kMaxBuckets (levels 2) or kWideBuckets (levels 1)
     int32_t seg_shift;      // segment of a cell = cell >> seg_shift (6..16; a segment's counts fit in LDS)
     int32_t sub_log2;       // segments per bucket = 1 << sub_log2 (bucket_shift - seg_shift, at most 10)
     int64_t n_segments;     // ceil(n_cells / 2^seg_shift)
@@ -90,6 +96,8 @@ struct Plan {
     int32_t *stpos;         // [n] staging slot of input particle i
     float4 *staging2;       // [n] segment order (cells of a segment together, unordered inside)
     int32_t *stage2_k;      // [n] staging slot of each segment-order slot
+    const float4 *seg_src;  // the segment order: staging2, or staging when buckets are segments
+    const int32_t *seg_k;   // stage2_k, or null when the staging slot is the segment-order slot
     uint2 *occ;             // [n_segments << (seg_shift - 5) + 2] per 32 cells: .x bit k: cell 32w + k
                             // holds a particle; .y the cstart index of the first occupied cell at or
                             // after cell 32w. Cell c starts at sorted slot
@@ -108,7 +116,7 @@ struct Plan {
     int2 *edges;            // [max_edges] linked pairs found by the sparse search
     int2 *bnd;              // domain mode: [max_edges] linked pairs across domains, then their root pairs
     unsigned int *edge_fill;   // [kEdgeSlices] pairs appended to each slice (may exceed its capacity)
-    unsigned long long *n_groups;  // [n_boxes]
+    unsigned long long *n_groups;  // [group_counts] groups of each box, in group_parts parts
     Counters *counters;
 
     int32_t *label;         // [n] output, input order
@@ -127,6 +135,10 @@ constexpr int kSegLog2Max = 16;
 constexpr int kSegLog2Auto = 16;      // largest segment the automatic choice takes
 constexpr int kSegTarget = 1365;      // default: about this many particles per segment
 constexpr int kMaxSubLog2 = 10;
+constexpr int kMaxBuckets = 256;
+constexpr int kWideBuckets = 1024;    // segments sorted in one level, without buckets
+constexpr int kOneSegment = 4080;     // particles up to which a single segment is sorted from the input
+constexpr int kFewTiles = 64;         // input tiles up to which the bucket pass scans its own counts
 
 constexpr int kItemFirst = INT32_MIN;   // the sign bit: counts stay below 2^31
 
@@ -135,6 +147,9 @@ constexpr int kItemFirst = INT32_MIN;   // the sign bit: counts stay below 2^31
 // the cell has been merged.
 constexpr int kCellOneGroup = 1;
 constexpr int kCellJoined = 2;
+
+constexpr int kGroupParts = 32;    // partial group counts over all boxes, when the boxes are fewer
+constexpr int kGroupStride = 16;   // 128 bytes
 
 // Capacity of the dense work-item list (fof_link.hip).
 int64_t max_dense_items(int64_t n, int dense_min);
@@ -154,7 +169,7 @@ struct KernelTimer {
 
 // Kernel launchers (fof_kernels.hip, fof_link.hip). All enqueue on `stream`;
 // `t` may be null.
-hipError_t launch_clear(const Plan &p, hipStream_t stream, KernelTimer *t);
+// Counters cleared and cells built.
 hipError_t launch_build(const Plan &p, hipStream_t stream, KernelTimer *t);
 // A second stream onto which the link phase may fork a kernel that is
 // independent of the others, with the events of the fork and of the join
@@ -175,6 +190,9 @@ hipError_t launch_finalize(const Plan &p, hipStream_t stream, KernelTimer *t);
 // p.bucket_hist[p.n_tiles].
 hipError_t launch_catalogue(const Plan &p, const int32_t *label, const int32_t *size, int min_size,
                             int32_t *g_first, int32_t *g_size, int32_t *g_box, int64_t capacity, hipStream_t stream);
+
+// The groups of box b from a host copy of Plan::n_groups.
+int64_t groups_of_box(const void *counts, const Plan &p, int32_t b);
 
 // One box of n particles on a workspace chosen by the caller (fof_api.cpp):
 // validates the options and the box like fof_workspace_bytes, returns in

@@ -39,6 +39,8 @@
 // predicate below must round every product and sum separately. The FP32
 // filter requests its fused multiply-adds explicitly (fmaf), which its error
 // bound allows.
+#include <type_traits>
+
 #include "fof_device.h"
 
 namespace fof {
@@ -50,18 +52,30 @@ constexpr int kScanItems = 8;                       // per thread
 constexpr int kScanTile = kBlock * kScanItems;      // 2048 counts per tile
 constexpr int kSortItems = 8;                       // input particles per thread
 constexpr int kSortTile = kBlock * kSortItems;      // 2048 input particles per tile
-constexpr int kMaxBuckets = 256;
 
 // ---------------------------------------------------------------- kernels --
 
-__global__ void __launch_bounds__(kBlock) k_clear(Plan p)
+// Particles per bucket, after the bucket histograms (levels 1 of many tiles).
+__device__ __forceinline__ int32_t *bucket_totals(const Plan &p) { return p.bucket_hist + p.n_buckets * p.n_tiles; }
+
+// The count of groups of box b to which work-group `block` adds: one address
+// takes an atomic every 14 ns or so, so a few boxes have several, in lines of
+// their own, summed when they are read.
+__device__ __forceinline__ unsigned long long *group_count(const Plan &p, int b, int block)
 {
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < p.n_segments; i += stride) p.seg_end[i] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < p.n_waves; i += stride) p.tile_dense[i] = 0ull;
-    int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t < p.n_boxes) p.n_groups[t] = 0;
-    if (t < kEdgeSlices) p.edge_fill[t] = 0;
+    return p.n_groups + (p.group_parts > 1 ? ((int64_t)b * p.group_parts + block % p.group_parts) * kGroupStride : b);
+}
+
+// What a run counts in, zeroed by the threads t of `threads`.
+__device__ __forceinline__ void clear_run(const Plan &p, int64_t t, int64_t threads)
+{
+    if (p.levels == 2)   // the segment pass counts in it; with fewer levels it is written whole
+        for (int64_t i = t; i < p.n_segments; i += threads) p.seg_end[i] = 0;
+    for (int64_t i = t; i < p.n_waves; i += threads) p.tile_dense[i] = 0ull;
+    if (p.levels == 1 && p.n_tiles > kFewTiles)
+        for (int64_t i = t; i < p.n_buckets; i += threads) bucket_totals(p)[i] = 0;
+    for (int64_t i = t; i < p.group_counts; i += threads) p.n_groups[i] = 0;
+    for (int64_t i = t; i < kEdgeSlices; i += threads) p.edge_fill[i] = 0;
     if (t == 0) {
         p.counters->pair_tests = 0;
         p.counters->links = 0;
@@ -79,6 +93,11 @@ __global__ void __launch_bounds__(kBlock) k_clear(Plan p)
     }
 }
 
+__global__ void __launch_bounds__(kBlock) k_clear(Plan p)
+{
+    clear_run(p, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+}
+
 // Cell key of input particle i; `ok` tells whether its coordinates are finite
 // and inside [0, L).
 __device__ __forceinline__ int64_t input_key(const Plan &p, int64_t i, float &x, float &y, float &z, bool &ok,
@@ -93,13 +112,26 @@ __device__ __forceinline__ int64_t input_key(const Plan &p, int64_t i, float &x,
     return particle_cell(bd, x, y, z);
 }
 
-// Bucket histogram of one tile, written bucket-major: hist[b * n_tiles + tile].
+// How the bucket pass places its tiles' runs.
+//  kScan: a scan over (bucket, tile) of the counts, written bucket-major;
+//  kFew: of at most kFewTiles tiles the scatter sums the counts itself
+//   (tile-major, so its loads are coalesced): two launches less;
+//  kTotals: (levels 1 with more tiles) every tile takes its place in its
+//   buckets with atomics on their totals (order inside a segment is free), and
+//   the scatter scans the totals: 3e5 particles 8 us instead of 46.
+enum Place { kScan, kFew, kTotals };
+
+// Bucket histogram of one tile; checks the coordinates. kFew: the run's
+// counters are cleared here too (one launch less), and the coordinates are
+// checked after them, in the scatter.
+template <int kBuckets, int kPlace>
 __global__ void __launch_bounds__(kBlock) k_bucket_hist(Plan p)
 {
     BoxHint hint;
-    __shared__ int cnt[kMaxBuckets];
+    __shared__ int cnt[kBuckets];
     const int64_t tile = blockIdx.x;
-    for (int b = threadIdx.x; b < kMaxBuckets; b += kBlock) cnt[b] = 0;
+    if constexpr (kPlace == kFew) clear_run(p, tile * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
+    for (int b = threadIdx.x; b < kBuckets; b += kBlock) cnt[b] = 0;
     __syncthreads();
     bool bad = false;
 #pragma unroll
@@ -113,29 +145,39 @@ __global__ void __launch_bounds__(kBlock) k_bucket_hist(Plan p)
             atomicAdd(&cnt[(int)(key >> p.bucket_shift)], 1);
         }
     }
-    if (__ballot(bad) && lane_id() == 0) atomicOr(&p.counters->error, 1u);
+    if (kPlace != kFew && __ballot(bad) && lane_id() == 0) atomicOr(&p.counters->error, 1u);
     __syncthreads();
-    for (int b = threadIdx.x; b < p.n_buckets; b += kBlock) p.bucket_hist[(int64_t)b * p.n_tiles + tile] = cnt[b];
+    for (int b = threadIdx.x; b < p.n_buckets; b += kBlock) {
+        if constexpr (kPlace == kScan) p.bucket_hist[(int64_t)b * p.n_tiles + tile] = cnt[b];
+        else if constexpr (kPlace == kFew) p.bucket_hist[tile * p.n_buckets + b] = cnt[b];
+        else if (cnt[b]) p.bucket_hist[tile * p.n_buckets + b] = atomicAdd(bucket_totals(p) + b, cnt[b]);
+    }
 }
 
 // Sorts one tile by bucket in LDS and writes each bucket's run to its place in
 // the staging order (x, y, z, original index as bits); stpos[i] = staging slot.
+// When the buckets are the segments themselves, the first tile's work-group
+// writes their ends.
+template <int kBuckets, int kPlace>
 __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
 {
     BoxHint hint;
+    constexpr int kPer = kBuckets / kBlock;   // buckets per thread: b = threadIdx.x * kPer + q
     __shared__ float4 stage[kSortTile];
-    __shared__ unsigned char stage_b[kSortTile];
-    __shared__ int cnt[kMaxBuckets], first[kMaxBuckets], dst0[kMaxBuckets];
+    using Bucket = std::conditional_t<(kBuckets > 256), unsigned short, unsigned char>;
+    __shared__ Bucket stage_b[kSortTile];
+    __shared__ int cnt[kBuckets], first[kBuckets], dst0[kBuckets];
     __shared__ int lds[kBlock / 64];
     // tiles go to XCDs in contiguous ranges: neighbouring tiles' runs share
     // cache lines of the staging buffer
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= p.n_tiles) return;
     const int64_t base = tile * kSortTile;
-    for (int b = threadIdx.x; b < kMaxBuckets; b += kBlock) cnt[b] = 0;
+    for (int b = threadIdx.x; b < kBuckets; b += kBlock) cnt[b] = 0;
     __syncthreads();
     float4 v[kSortItems];
     int bk[kSortItems], rk[kSortItems];
+    bool bad = false;
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = base + k * kBlock + threadIdx.x;
@@ -144,18 +186,65 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
             float x, y, z;
             bool ok;
             const int64_t key = input_key(p, i, x, y, z, ok, hint);
+            bad |= !ok;
             bk[k] = (int)(key >> p.bucket_shift);
             rk[k] = atomicAdd(&cnt[bk[k]], 1);
             v[k] = make_float4(x, y, z, __int_as_float((int)i));
         }
     }
+    if (kPlace == kFew && __ballot(bad) && lane_id() == 0) atomicOr(&p.counters->error, 1u);
     __syncthreads();
     {
-        const int b = threadIdx.x;   // kBlock == kMaxBuckets: one bucket per thread
+        const int b0 = (int)threadIdx.x * kPer;
+        int c[kPer], at[kPer], all[kPer];
+        int sum = 0, sum_all = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            c[q] = cnt[b0 + q];
+            sum += c[q];
+            at[q] = all[q] = 0;
+        }
+        if constexpr (kPlace == kFew) {
+            constexpr int kAhead = 8;   // tiles whose counts are read together
+            for (int t0 = 0; t0 < (int)p.n_tiles; t0 += kAhead) {
+                int h[kAhead][kPer];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q)
+                        h[u][q] = t0 + u < (int)p.n_tiles && b0 + q < p.n_buckets
+                                      ? p.bucket_hist[(int64_t)(t0 + u) * p.n_buckets + b0 + q] : 0;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) {
+                        all[q] += h[u][q];
+                        at[q] += t0 + u < tile ? h[u][q] : 0;
+                    }
+            }
+        } else if constexpr (kPlace == kTotals) {
+#pragma unroll
+            for (int q = 0; q < kPer; ++q)
+                if (b0 + q < p.n_buckets) {
+                    all[q] = bucket_totals(p)[b0 + q];
+                    at[q] = p.bucket_hist[tile * p.n_buckets + b0 + q];   // unused unless c[q] > 0
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) sum_all += all[q];
         int total;
-        const int c = cnt[b];
-        first[b] = block_excl_scan<kBlock>(c, lds, &total);
-        dst0[b] = b < p.n_buckets ? p.bucket_hist[(int64_t)b * p.n_tiles + tile] : 0;
+        int run = block_excl_scan<kBlock>(sum, lds, &total);
+        int run_all = kPlace != kScan ? block_excl_scan<kBlock>(sum_all, lds, &total) : 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int b = b0 + q;
+            first[b] = run;
+            run += c[q];
+            if (b >= p.n_buckets) continue;
+            dst0[b] = kPlace != kScan ? run_all + at[q] : p.bucket_hist[(int64_t)b * p.n_tiles + tile];
+            run_all += all[q];
+            if (kPlace != kScan && tile == 0) p.seg_end[b] = run_all;
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -163,7 +252,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
         if (bk[k] >= 0) {
             const int at = first[bk[k]] + rk[k];
             stage[at] = v[k];
-            stage_b[at] = (unsigned char)bk[k];
+            stage_b[at] = (Bucket)bk[k];
         }
     __syncthreads();
     const int count = (int)min((int64_t)kSortTile, p.n - base);
@@ -172,7 +261,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
         const int b = stage_b[j];
         const int dst = dst0[b] + (j - first[b]);
         p.staging[dst] = e;
-        p.stpos[__float_as_int(e.w)] = dst;
+        if (!p.direct) p.stpos[__float_as_int(e.w)] = dst;
     }
 }
 
@@ -380,6 +469,7 @@ constexpr int kOrderCap = 4080;          // segments up to this many particles a
 constexpr int kCntCap = 4080;            // occupied cells counted at once (a window of ranks)
 constexpr int kDenseWords = kOrderCap / 64 + 2;   // 64-slot masks a segment placed through LDS can touch
 static_assert(kDenseWords * 4 <= kOrderCap, "the masks fit where the slot order goes");
+static_assert(kOneSegment <= kOrderCap, "a segment sorted from the input is placed through LDS");
 static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window");
 
 // One work-group per segment of 2^seg_shift consecutive cells, whose P
@@ -409,8 +499,11 @@ static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window"
 // kWordsMax: the occupancy words of the largest segment this instance takes
 // (segments of up to 2^14 cells: one word per thread, the smaller LDS
 // footprint; above: several per thread).
-template <int kWordsMax>
-__global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(kWordsMax <= 1024 ? 8 : 6))) k_cell_sort(Plan p)
+// kInput: the one segment of a run of at most kOneSegment particles, read from
+// the input itself: this launch is then the whole build (it clears the run's
+// counters and checks the coordinates too).
+template <int kWordsMax, bool kInput>
+__global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(kWordsMax <= 1024 && !kInput ? 8 : 6))) k_cell_sort(Plan p)
 {
     BoxHint hint;
     constexpr int kWordsPerThread = (kWordsMax + kSegBlock - 1) / kSegBlock;
@@ -425,15 +518,23 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
     const int j = (int)blockIdx.x;
     const int words = 1 << (p.seg_shift - 5);
     const int64_t cell0 = (int64_t)j << p.seg_shift;
-    const int a = j ? p.seg_end[j - 1] : 0;
-    const int e = p.seg_end[j];
+    const int a = !kInput && j ? p.seg_end[j - 1] : 0;
+    const int e = kInput ? (int)p.n : p.seg_end[j];
     const int P = e - a;
     const int tid = (int)threadIdx.x;
-    const bool through_lds = P <= kOrderCap;
+    const bool through_lds = kInput || P <= kOrderCap;
+    auto source = [&](int k) {   // particle k of the segment order
+        if constexpr (kInput) {
+            return make_float4(p.pos[3 * k], p.pos[3 * k + 1], p.pos[3 * k + 2], __int_as_float(k));
+        } else {
+            return p.seg_src[k];
+        }
+    };
+    auto slot_of = [&](int k) { return p.seg_k ? p.seg_k[k] : k; };   // its staging slot
     const int seg_cells = words << 5;
     // dense slots of a segment placed through LDS (step 5), before its slot order (step 6)
     unsigned long long *dense = reinterpret_cast<unsigned long long *>(order);
-    bool bad = false;
+    bool bad = false, outside = false;
     // the segment's cell of a staged particle; a cell outside the segment
     // cannot happen with a consistent partition and is latched, not used
     auto local_cell = [&](const float4 &v) {
@@ -444,6 +545,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         }
         return (int)c;
     };
+    if constexpr (kInput) clear_run(p, tid, kSegBlock);
     for (int w = tid; w < words; w += kSegBlock) bits[w] = 0u;
     __syncthreads();
 
@@ -452,11 +554,15 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         float4 v[kSegUnroll];
 #pragma unroll
         for (int q = 0; q < kSegUnroll; ++q)
-            if (k0 + q * kSegBlock < e) v[q] = p.staging2[k0 + q * kSegBlock];
+            if (k0 + q * kSegBlock < e) v[q] = source(k0 + q * kSegBlock);
 #pragma unroll
         for (int q = 0; q < kSegUnroll; ++q)
             if (k0 + q * kSegBlock < e) {
                 const int c = local_cell(v[q]);
+                if constexpr (kInput) {
+                    const double L = box_of(p, p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, __float_as_int(v[q].w), hint)).L;
+                    outside |= !(in_box(v[q].x, L) && in_box(v[q].y, L) && in_box(v[q].z, L));
+                }
                 atomicOr(&bits[c >> 5], 1u << (c & 31));
                 if (through_lds) lrank[k0 + q * kSegBlock - a] = (unsigned short)c;
             }
@@ -516,7 +622,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                 float4 v[kCountUnroll];
 #pragma unroll
                 for (int q = 0; q < kCountUnroll; ++q)
-                    if (k0 + q * kSegBlock < e) v[q] = p.staging2[k0 + q * kSegBlock];
+                    if (k0 + q * kSegBlock < e) v[q] = source(k0 + q * kSegBlock);
 #pragma unroll
                 for (int q = 0; q < kCountUnroll; ++q)
                     if (k0 + q * kSegBlock < e) {
@@ -618,8 +724,8 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
                 for (int q = 0; q < kPlaceUnroll; ++q)
                     if (k0 + q * kSegBlock < e) {
-                        v[q] = p.staging2[k0 + q * kSegBlock];
-                        kk[q] = p.stage2_k[k0 + q * kSegBlock];
+                        v[q] = source(k0 + q * kSegBlock);
+                        kk[q] = p.direct ? 0 : slot_of(k0 + q * kSegBlock);
                     }
 #pragma unroll
                 for (int q = 0; q < kPlaceUnroll; ++q) {
@@ -638,7 +744,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                     p.gmin[dst] = i;
                     p.parent[dst] = dst;
                     p.gsize[dst] = 1;
-                    p.kmap[dst] = kk[q];
+                    if (!p.direct) p.kmap[dst] = kk[q];
                 }
             }
         }
@@ -653,6 +759,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         if (tid < 2) p.occ[((int64_t)gridDim.x << (p.seg_shift - 5)) + tid] = make_uint2(0u, (unsigned)p.n);
     }
     if (__ballot(bad) && lane_id() == 0) atomicOr(&p.counters->error, 2u);
+    if (kInput && __ballot(outside) && lane_id() == 0) atomicOr(&p.counters->error, 1u);
     if (!through_lds) return;
     __syncthreads();
     for (int d0 = tid; d0 < P; d0 += kSegUnroll * kSegBlock) {
@@ -662,8 +769,8 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         for (int q = 0; q < kSegUnroll; ++q)
             if (d0 + q * kSegBlock < P) {
                 from[q] = a + order[d0 + q * kSegBlock];
-                v[q] = p.staging2[from[q]];
-                k_of[q] = p.stage2_k[from[q]];
+                v[q] = source(from[q]);
+                k_of[q] = p.direct ? 0 : slot_of(from[q]);
             }
 #pragma unroll
         for (int q = 0; q < kSegUnroll; ++q)
@@ -675,7 +782,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                 p.gmin[dst] = i;
                 p.parent[dst] = dst;
                 p.gsize[dst] = 1;
-                p.kmap[dst] = k_of[q];
+                if (!p.direct) p.kmap[dst] = k_of[q];
             }
     }
 }
@@ -819,13 +926,53 @@ __device__ __forceinline__ void resolve_tile(const Plan &p, int64_t s64)
         if (lane_id() == 0 && wave < p.n_waves) p.wave_roots[wave] = roots;
     } else {
         if (lane_id() == 0 && wave < p.n_waves) p.wave_roots[wave] = 0;
-        if (root) atomicAdd(p.n_groups + b, 1ull);
+        if (root) atomicAdd(group_count(p, b, blockIdx.x), 1ull);
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_resolve(Plan p)
 {
     resolve_tile(p, xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x);
+}
+
+// Resolve straight into input order (Plan::direct): while the outputs fit in
+// the caches the scattered 4-byte writes cost less than staging slots, their
+// two maps in the sort, a group count and a gather, each a launch. A
+// persistent grid, so that each box's count takes few atomics.
+__global__ void __launch_bounds__(kBlock) k_resolve_direct(Plan p)
+{
+    BoxHint hint;
+    int box = -1, roots = 0;   // roots counted in box `box`, the same in every lane
+    const int64_t tiles = (p.n + 63) / 64;
+    const XcdRange xr = xcd_range(tiles, kBlock / 64, threadIdx.x >> 6);
+    for (int64_t tile = xr.first; tile < xr.end; tile += xr.stride) {
+        const int64_t s64 = tile * 64 + lane_id();
+        bool root = false;
+        int b = 0;
+        if (s64 < p.n) {
+            const int s = (int)s64;
+            b = p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, s64, hint);
+            const int r = p.parent[s];
+            const int o = p.orig[s];
+            const int m = p.gmin[r];
+            const int p0 = p.n_boxes == 1 ? 0 : (int)p.box_p0[b];
+            p.label[o] = m - p0;
+            p.size[o] = o == m ? p.gsize[r] : 0;
+            root = r == s;
+        }
+        const int b0 = __builtin_amdgcn_readfirstlane(b);
+        if (__ballot(s64 < p.n && b != b0) == 0) {
+            if (b0 != box) {
+                if (roots && lane_id() == 0) atomicAdd(group_count(p, box, blockIdx.x), (unsigned long long)roots);
+                box = b0;
+                roots = 0;
+            }
+            roots += __popcll(__ballot(root));
+        } else if (root) {
+            atomicAdd(group_count(p, b, blockIdx.x), 1ull);
+        }
+    }
+    if (roots && lane_id() == 0) atomicAdd(group_count(p, box, blockIdx.x), (unsigned long long)roots);
 }
 
 // n_groups[box] += sum of wave_roots over the waves of the box (a wave belongs
@@ -852,7 +999,7 @@ __global__ void __launch_bounds__(kBlock) k_group_count(Plan p)
         if (threadIdx.x == 0) {
             unsigned long long t = 0;
             for (int k = 0; k < kBlock / 64; ++k) t += part[k];
-            if (t) atomicAdd(p.n_groups, t);
+            if (t) atomicAdd(group_count(p, 0, blockIdx.x), t);
         }
         return;
     }
@@ -865,7 +1012,7 @@ __global__ void __launch_bounds__(kBlock) k_group_count(Plan p)
             v = (unsigned)p.wave_roots[w];
             if (v) key = find_box(p.box_p0, p.n_boxes, w << 6);
         }
-        wave_add_by_key(p.n_groups, key, v);
+        wave_add_by_key(group_count(p, 0, blockIdx.x), key < 0 || p.group_parts == 1 ? key : key * p.group_parts * kGroupStride, v);
     }
 }
 
@@ -892,7 +1039,7 @@ __global__ void __launch_bounds__(kBlock) k_relink_reset(Plan p)
         p.gmin[s] = p.orig[s];
     }
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t < p.n_boxes) p.n_groups[t] = 0;
+    for (int64_t i = t; i < p.group_counts; i += stride) p.n_groups[i] = 0;
     if (t < kEdgeSlices) p.edge_fill[t] = 0;
     if (t == 0) {
         p.counters->pair_tests = 0;
@@ -965,6 +1112,7 @@ inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBloc
 // Grid of the persistent flatten: a few work-groups per compute unit, each
 // looping over tiles (measured faster than one work-group per tile).
 constexpr int64_t kStreamBlocks = 2048;
+constexpr int64_t kDirectBlocks = 512;
 inline int64_t grid_tiles(int64_t n) { return (n + kBlock - 1) / kBlock; }
 
 }  // namespace
@@ -1013,38 +1161,54 @@ int64_t scan_scratch_for(int64_t len)
 
 int64_t sort_tiles_for(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
 
-hipError_t launch_clear(const Plan &p, hipStream_t stream, KernelTimer *t)
-{
-    int64_t work = p.n_segments > p.n_boxes ? p.n_segments : p.n_boxes;
-    if (work < p.n_waves) work = p.n_waves;
-    if (work < kEdgeSlices) work = kEdgeSlices;
-    unsigned g = grid_for(work);
-    if (g > 65536u) g = 65536u;
-    FOF_TIMED(K_CLEAR, hipLaunchKernelGGL(k_clear, dim3(g), dim3(kBlock), 0, stream, p));
-    return hipGetLastError();
-}
-
 hipError_t launch_build(const Plan &p, hipStream_t stream, KernelTimer *t)
 {
+    // cleared by the first kernel of a small build, otherwise on its own
+    const bool few = p.levels == 1 && p.n_tiles <= kFewTiles;
+    const bool clear_alone = p.n == 0 || (p.levels > 0 && !few);
+    if (clear_alone) {
+        int64_t work = p.n_segments > p.n_boxes ? p.n_segments : p.n_boxes;
+        if (work < p.n_waves) work = p.n_waves;
+        if (work < kEdgeSlices) work = kEdgeSlices;
+        unsigned g = grid_for(work);
+        if (g > 65536u) g = 65536u;
+        FOF_TIMED(K_CLEAR, hipLaunchKernelGGL(k_clear, dim3(g), dim3(kBlock), 0, stream, p));
+    }
+    const dim3 grid((unsigned)p.n_segments), block(kSegBlock);
+    if (p.levels == 0 && p.n > 0) {
+        hipLaunchKernelGGL((k_cell_sort<(1 << kSegLog2Max) / 32, true>), grid, block, 0, stream, p);
+        return hipGetLastError();
+    }
     const unsigned seg_tiles = xcd_grid(p.n_tiles + p.n_buckets);
     if (p.n > 0) {
-        const unsigned tiles = (unsigned)p.n_tiles;
-        FOF_TIMED(K_BUCKET_HIST, hipLaunchKernelGGL(k_bucket_hist, dim3(tiles), dim3(kBlock), 0, stream, p));
-        FOF_TIMED(K_BUCKET_SCAN, scan_exclusive(p.bucket_hist, (int64_t)p.n_buckets * p.n_tiles, p.scan_part, stream));
-        FOF_TIMED(K_BUCKET_SCATTER,
-                  hipLaunchKernelGGL(k_bucket_scatter, dim3(xcd_grid(tiles)), dim3(kBlock), 0, stream, p));
-        FOF_TIMED(K_SEG_HIST, hipLaunchKernelGGL(k_seg_hist, dim3(seg_tiles), dim3(kBlock), 0, stream, p));
+        const dim3 tiles((unsigned)p.n_tiles), xtiles(xcd_grid(p.n_tiles)), b(kBlock);
+        const int64_t hist_len = (int64_t)p.n_buckets * p.n_tiles;
+        if (few) {
+            hipLaunchKernelGGL((k_bucket_hist<kWideBuckets, kFew>), tiles, b, 0, stream, p);
+            hipLaunchKernelGGL((k_bucket_scatter<kWideBuckets, kFew>), xtiles, b, 0, stream, p);
+        } else if (p.levels == 1) {
+            hipLaunchKernelGGL((k_bucket_hist<kWideBuckets, kTotals>), tiles, b, 0, stream, p);
+            hipLaunchKernelGGL((k_bucket_scatter<kWideBuckets, kTotals>), xtiles, b, 0, stream, p);
+        } else {
+            FOF_TIMED(K_BUCKET_HIST,
+                      hipLaunchKernelGGL((k_bucket_hist<kMaxBuckets, kScan>), tiles, b, 0, stream, p));
+            FOF_TIMED(K_BUCKET_SCAN, scan_exclusive(p.bucket_hist, hist_len, p.scan_part, stream));
+            FOF_TIMED(K_BUCKET_SCATTER,
+                      hipLaunchKernelGGL((k_bucket_scatter<kMaxBuckets, kScan>), xtiles, b, 0, stream, p));
+            FOF_TIMED(K_SEG_HIST, hipLaunchKernelGGL(k_seg_hist, dim3(seg_tiles), b, 0, stream, p));
+        }
     }
-    FOF_TIMED(K_SEG_SCAN, scan_exclusive(p.seg_end, p.n_segments, p.scan_part, stream));
-    if (p.n > 0)
+    if (p.levels == 2 || p.n == 0)
+        FOF_TIMED(K_SEG_SCAN, scan_exclusive(p.seg_end, p.n_segments, p.scan_part, stream));
+    if (p.levels == 2 && p.n > 0)
         FOF_TIMED(K_SEG_SCATTER, hipLaunchKernelGGL(k_seg_scatter, dim3(seg_tiles), dim3(kBlock), 0, stream, p));
-    const dim3 grid((unsigned)p.n_segments), block(kSegBlock);
     if (p.seg_shift <= 14)
-        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL(k_cell_sort<(1 << 14) / 32>, grid, block, 0, stream, p));
+        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL((k_cell_sort<(1 << 14) / 32, false>), grid, block, 0, stream, p));
     else if (p.seg_shift == 15)
-        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL(k_cell_sort<(1 << 15) / 32>, grid, block, 0, stream, p));
+        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL((k_cell_sort<(1 << 15) / 32, false>), grid, block, 0, stream, p));
     else
-        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL(k_cell_sort<(1 << kSegLog2Max) / 32>, grid, block, 0, stream, p));
+        FOF_TIMED(K_CELL_SORT,
+                  hipLaunchKernelGGL((k_cell_sort<(1 << kSegLog2Max) / 32, false>), grid, block, 0, stream, p));
     return hipGetLastError();
 }
 
@@ -1080,6 +1244,12 @@ hipError_t launch_finalize(const Plan &p, hipStream_t stream, KernelTimer *t)
     const unsigned flatten_grid = (unsigned)min(kStreamBlocks, grid_tiles(p.n));
     if (p.stats) hipLaunchKernelGGL(k_find_depth, dim3(flatten_grid), dim3(kBlock), 0, stream, p);
     FOF_TIMED(K_FLATTEN, hipLaunchKernelGGL(k_flatten, dim3(flatten_grid), dim3(kBlock), 0, stream, p));
+    if (p.direct) {
+        int64_t g = (p.n + kBlock - 1) / kBlock;
+        if (g > kDirectBlocks) g = kDirectBlocks;
+        hipLaunchKernelGGL(k_resolve_direct, dim3(xcd_grid(g)), dim3(kBlock), 0, stream, p);
+        return hipGetLastError();
+    }
     FOF_TIMED(K_RESOLVE, {
         hipLaunchKernelGGL(k_resolve, dim3(xcd_grid(grid_tiles(p.n))), dim3(kBlock), 0, stream, p);
         hipLaunchKernelGGL(k_group_count, dim3((unsigned)((p.n_waves + kGroupRun - 1) / kGroupRun)), dim3(kBlock), 0,

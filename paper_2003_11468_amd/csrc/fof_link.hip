@@ -236,6 +236,9 @@ __device__ __forceinline__ void row_spans(const int st[3], const int en[3], cons
 // union kernel then merges all of them with one thread per pair.
 constexpr int kEdgeBuf = 128;
 
+// kInline: a wave merges its pairs itself, 64 at a time, instead (small runs,
+// where the union kernel's launch costs more than the waiting).
+template <bool kInline>
 struct EdgeSink {
     int2 *buf;      // this wave's LDS buffer [kEdgeBuf]
     int count;      // wave-uniform fill level
@@ -261,6 +264,13 @@ struct EdgeSink {
     {
         if (count == 0) return;
         const int lane = lane_id();
+        if constexpr (kInline) {
+            for (int k = lane; k < count; k += 64)
+                retries += unite(p.parent, buf[k].x, buf[k].y, p.link_random, p.find_mode);
+            __builtin_amdgcn_wave_barrier();
+            count = 0;
+            return;
+        }
         const int slice = blockIdx.x % kEdgeSlices;
         const int64_t cap = p.max_edges / kEdgeSlices;
         unsigned base = 0;
@@ -306,8 +316,8 @@ struct BoxPair {
 // wave's T pairs, finds the unit of its first pair by one binary search, then
 // walks forward; every lane runs the same number of steps. kOneBox: every
 // home particle of the tile lies in one box, whose parameters are `bp`.
-template <bool kFP64, bool kStats, bool kOneBox>
-__device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSink &sink, int s0, int n_units,
+template <bool kFP64, bool kStats, bool kOneBox, bool kInline>
+__device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSink<kInline> &sink, int s0, int n_units,
                                              int n_pairs, int b, BoxPair bp, bool in_tile, unsigned long long &tests,
                                              unsigned long long &links, unsigned long long &band, unsigned &retries)
 {
@@ -417,13 +427,12 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
     }
 }
 
-template <bool kFP64, bool kStats>
-__global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
+// The per-particle search by work-group `block` of `blocks`, on this wave's LDS.
+template <bool kFP64, bool kStats, bool kInline>
+__device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int block, int blocks)
 {
-    __shared__ SparseLds lds[kWaves];
     const int wid = threadIdx.x >> 6, lane = lane_id();
-    SparseLds &L = lds[wid];
-    EdgeSink sink{L.ebuf, 0};
+    EdgeSink<kInline> sink{L.ebuf, 0};
     unsigned long long tests = 0, links = 0, band = 0;
     unsigned retries = 0;
     // links inside a tile are joined by the search itself (index order only:
@@ -440,7 +449,7 @@ __global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
     const int64_t n_tiles = (p.n + 63) / 64;
     // each XCD sweeps one contiguous range of tiles, so the neighbour rows of
     // consecutive tiles are reused from its own L2
-    const XcdRange xr = xcd_range(n_tiles, kWaves, wid);
+    const XcdRange xr = xcd_range(n_tiles, kWaves, wid, block, blocks);
     for (int64_t tile = xr.first; tile < xr.end; tile += xr.stride) {
         // a tile whose slots all lie in dense cells has nothing to search here
         // (slots past the end count as dense)
@@ -623,10 +632,10 @@ __global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
         const int s0 = (int)(tile * 64);
         const int b0 = __builtin_amdgcn_readfirstlane(b);
         if (__ballot(b != b0) == 0)
-            sparse_pairs<kFP64, kStats, true>(p, L, sink, s0, n_units, n_pairs, b, BoxPair::of(box_of(p, b0)),
+            sparse_pairs<kFP64, kStats, true, kInline>(p, L, sink, s0, n_units, n_pairs, b, BoxPair::of(box_of(p, b0)),
                                               tile_union, tests, links, band, retries);
         else
-            sparse_pairs<kFP64, kStats, false>(p, L, sink, s0, n_units, n_pairs, b, BoxPair{}, tile_union, tests,
+            sparse_pairs<kFP64, kStats, false, kInline>(p, L, sink, s0, n_units, n_pairs, b, BoxPair{}, tile_union, tests,
                                                links, band, retries);
         __builtin_amdgcn_wave_barrier();
         if (tile_union) {
@@ -669,6 +678,13 @@ __global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
             atomicAdd(&p.counters->cas_retries, r);
         }
     }
+}
+
+template <bool kFP64, bool kStats>
+__global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
+{
+    __shared__ SparseLds lds[kWaves];
+    sparse_search<kFP64, kStats, false>(p, lds[threadIdx.x >> 6], blockIdx.x, gridDim.x);
 }
 
 constexpr int kUnionIlp = 8;   // queued pairs a lane merges at once
@@ -1234,21 +1250,26 @@ __device__ __forceinline__ unsigned long long cell_rows(const BoxDev &bd, int n,
     return ((((unsigned long long)hi) << 32) | lo) | (1ull << lane_id());
 }
 
+// Per-wave LDS of the pre-merge.
+struct PremergeLds {
+    unsigned long long rep[kMaxSub];   // per sub-cell: (hooking key << 32 | particle) of its first
+                                       // particle, ~0 when empty
+    int join[kMaxSub];                 // forest over the sub-cells (sub_adj)
+    int used[kMaxSub];                 // the occupied sub-cells (sub_adj)
+};
+
+// The pre-merge by work-group `block` of `blocks`, on this wave's LDS.
 template <bool kFP64>
-__global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
+__device__ __forceinline__ void premerge_cells(const Plan &p, PremergeLds &L, int block, int blocks)
 {
-    // per sub-cell: (hooking key << 32 | particle) of its first particle, ~0 when empty
-    __shared__ unsigned long long rep[kWaves][kMaxSub];
-    __shared__ int join[kWaves][kMaxSub];   // forest over the sub-cells (sub_adj)
-    __shared__ int used[kWaves][kMaxSub];   // the occupied sub-cells (sub_adj)
     const int wid = threadIdx.x >> 6, lane = lane_id();
-    unsigned long long *rp = rep[wid];
-    int *jf = join[wid];
-    int *ul = used[wid];
+    unsigned long long *rp = L.rep;
+    int *jf = L.join;
+    int *ul = L.used;
     const bool rnd = p.link_random != 0;
     constexpr unsigned long long kEmpty = ~0ull;
     const int n_items = (int)p.counters->n_items;
-    const XcdRange xr = xcd_range(n_items, kWaves, wid);
+    const XcdRange xr = xcd_range(n_items, kWaves, wid, block, blocks);
     for (int64_t it = xr.first; it < xr.end; it += xr.stride) {
         const int4 item = p.items[it];
         const int cs = __builtin_amdgcn_readfirstlane(item.x);
@@ -1391,6 +1412,30 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
         if (lane == 0) p.sorted[cs].w = __int_as_float(one ? kCellJoined | kCellOneGroup : 0);
         __builtin_amdgcn_wave_barrier();
     }
+}
+
+template <bool kFP64>
+__global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
+{
+    __shared__ PremergeLds lds[kWaves];
+    premerge_cells<kFP64>(p, lds[threadIdx.x >> 6], blockIdx.x, gridDim.x);
+}
+
+// Small runs (Plan::fused_link): the per-particle search, merging its own
+// links, and the pre-merge side by side in one launch (they touch disjoint
+// sets of particles) instead of three. The first `search` work-groups search.
+template <bool kFP64>
+__global__ void __launch_bounds__(kBlock) k_link_small(Plan p, int search)
+{
+    union Lds {
+        SparseLds sparse[kWaves];
+        PremergeLds pre[kWaves];
+    };
+    __shared__ __align__(16) unsigned char raw[sizeof(Lds)];
+    Lds &lds = *reinterpret_cast<Lds *>(raw);
+    const int wid = threadIdx.x >> 6, block = blockIdx.x;
+    if (block < search) sparse_search<kFP64, false, true>(p, lds.sparse[wid], block, search);
+    else premerge_cells<kFP64>(p, lds.pre[wid], block - search, gridDim.x - search);
 }
 
 // Global merge of domain mode, after the search. Workspace: the segment-order
@@ -1563,7 +1608,7 @@ __global__ void __launch_bounds__(kBlock) k_link_rest(Plan p)
 {
     __shared__ int2 ebuf[kWaves][kEdgeBuf];
     const int wid = threadIdx.x >> 6, lane = lane_id();
-    EdgeSink sink{ebuf[wid], 0};
+    EdgeSink<false> sink{ebuf[wid], 0};
     unsigned long long tests = 0, links = 0, band = 0;
     unsigned retries = 0;
     const bool rnd = p.link_random != 0;
@@ -1650,6 +1695,19 @@ hipError_t launch_link_t(const Plan &p, hipStream_t stream, KernelTimer *t, cons
 {
     Plan first = p;
     first.sample = p.giant_skip;   // the giant-component skip starts from the axis links
+    if constexpr (!kStats)
+        if (p.fused_link && !t) {
+            const unsigned search = xcd_grid((p.n + 64 * kWaves - 1) / (64 * kWaves));
+            const unsigned items = xcd_grid((p.n / p.dense_min + kWaves) / kWaves);
+            const unsigned pre = items < 256u ? items : 256u;
+            hipLaunchKernelGGL((k_link_small<kFP64>), dim3(search + pre), dim3(kBlock), 0, stream, p, (int)search);
+            const unsigned dense = items < (unsigned)p.dense_blocks ? items : (unsigned)p.dense_blocks;
+            if (p.link_random)
+                hipLaunchKernelGGL((k_link_dense<kFP64, false, true>), dim3(dense), dim3(kBlock), 0, stream, p);
+            else
+                hipLaunchKernelGGL((k_link_dense<kFP64, false, false>), dim3(dense), dim3(kBlock), 0, stream, p);
+            return hipSuccess;
+        }
     if (t) t->mark(K_LINK_SPARSE, false, stream);
     hipLaunchKernelGGL((k_link_sparse<kFP64, kStats>), dim3((unsigned)p.sparse_blocks), dim3(kBlock), 0, stream,
                        first);

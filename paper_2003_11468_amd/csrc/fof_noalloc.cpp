@@ -71,22 +71,22 @@ extern "C" fof_status fof_label_noalloc(const fof_options *opt, void *hip_stream
     p.label = d_group_index;
     p.size = d_group_size;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    // every array the run reads is written by it first (k_clear zeroes the
-    // counters, group counts and segment counts), so the previous call's
-    // contents do not matter
-    hipError_t e = fof::launch_clear(p, s, nullptr);
-    if (e == hipSuccess) e = fof::launch_build(p, s, nullptr);
+    // every array the run reads is written by it first (the build zeroes what
+    // it counts in before anything is added), so the previous call's contents
+    // do not matter
+    hipError_t e = fof::launch_build(p, s, nullptr);
     if (e == hipSuccess) e = fof::launch_link(p, s, nullptr);
     if (e == hipSuccess) e = fof::launch_finalize(p, s, nullptr);
     if (e != hipSuccess) return FOF_ERR_DEVICE;
     if (!h_n_groups) return FOF_OK;
-    unsigned long long groups = 0;
+    unsigned long long groups[fof::kGroupParts * fof::kGroupStride];
     unsigned int error = 0;
-    if (hipMemcpyAsync(&groups, p.n_groups, sizeof(groups), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    if (hipMemcpyAsync(groups, p.n_groups, sizeof(groups[0]) * (size_t)p.group_counts, hipMemcpyDeviceToHost, s) !=
+            hipSuccess ||
         hipMemcpyAsync(&error, &p.counters->error, sizeof(error), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return FOF_ERR_DEVICE;
-    *h_n_groups = (int64_t)groups;
+    *h_n_groups = fof::groups_of_box(groups, p, 0);
     if (error & 2u) return FOF_ERR_DEVICE;
     return (error & 1u) ? FOF_ERR_OUT_OF_BOX : FOF_OK;
 }

@@ -1,0 +1,88 @@
+"""Small runs take fewer launches (one segment sorted from the input, one sort
+level, links merged by the search, results straight to input order): each of
+those ways, around the sizes where one gives way to the next, against the CPU
+oracle, through the workspace path, the no-allocation entry point and replays
+of a captured graph.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+fof = pytest.importorskip("paper_2003_11468_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+def same(got, ref):
+    return (np.array_equal(got[0].cpu().numpy(), ref[0]) and np.array_equal(got[1].cpu().numpy(), ref[1])
+            and int(got[2]) == ref[2])
+
+
+@pytest.mark.parametrize("predicate", ["fp32_filter", "fp64"])
+@pytest.mark.parametrize("n", [1, 64, 2049, 4080, 4081, 131072, 131073])
+def test_sizes_where_the_launches_change(n, predicate):
+    pos_np = synth.clustered(n, 30 + n % 97, 0, 0.6)
+    lx = synth.linking_length(0.2, n) if n > 8 else 0.1
+    ref, ref_short = oracle.fof(pos_np, lx), oracle.fof(pos_np, 0.7 * lx)
+    pos = torch.from_numpy(pos_np).cuda()
+    for kw in (dict(), dict(cell_factor=1.375, dense_min=16), dict(link_order="random"), dict(compression="depth2"),
+               dict(stats=True), dict(timings=True), dict(segment_log2=8)):
+        f = fof.FoF(predicate, **kw)
+        try:
+            label, size, ng = f.run(pos, [0, n], 1.0, lx)
+            assert same((label, size, ng[0]), ref), kw
+            label, size, ng = f.relink(0.7 * lx, 1)
+            assert same((label, size, ng[0]), ref_short), kw
+        finally:
+            f.close()
+    label, size = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    ng = fof.fof_label_noalloc(pos, 1.0, lx, label, size, fof.make_options(predicate=predicate),
+                               torch.cuda.current_stream().cuda_stream)
+    assert same((label, size, ng), ref)
+
+
+@pytest.mark.parametrize("sizes", [[3, 0, 1, 700, 5], [1500] * 40, [60_000, 70_000], [200_000, 1, 120_000]])
+def test_batches_in_replayed_graphs(sizes):
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(offsets[-1])
+    lx = np.array([synth.linking_length(0.2, s) if s > 8 else 0.1 for s in sizes])
+    pos = torch.empty(n, 3, dtype=torch.float32, device="cuda")
+    label, size = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    f = fof.FoF()
+    try:
+        for seed in range(3):   # new positions for each replay, eager work between
+            p = np.concatenate([synth.clustered(s, 50 + seed, k, 0.6) for k, s in enumerate(sizes)])
+            ref = oracle.fof_boxes(p, offsets, np.ones(len(sizes)), lx)
+            pos.copy_(torch.from_numpy(p))
+            if seed == 0:
+                f.capture(pos, offsets, 1.0, lx, label, size)
+            f.replay()
+            ng = f.n_groups(len(sizes))
+            assert np.array_equal(label.cpu().numpy(), ref[0]) and np.array_equal(size.cpu().numpy(), ref[1])
+            assert np.array_equal(ng, ref[2])
+            eager = f.run(pos, offsets, 1.0, lx)
+            assert torch.equal(eager[0], label) and torch.equal(eager[1], size) and np.array_equal(eager[2], ref[2])
+    finally:
+        f.close()
+
+
+@pytest.mark.parametrize("n", [1000, 30_000, 200_000, 1_200_000])
+def test_coordinates_are_checked_in_every_build(n):
+    pos = torch.rand(n, 3, device="cuda") * 0.99
+    f = fof.FoF()
+    try:
+        lx = synth.linking_length(0.2, n)
+        for bad in (1.0, float("nan"), -1e-3):
+            broken = pos.clone()
+            broken[n - 1, 1] = bad
+            with pytest.raises(fof.FoFError) as e:
+                f.run(broken, [0, n], 1.0, lx)
+            assert e.value.status == fof.FOF_ERR_OUT_OF_BOX
+            f.run(pos, [0, n], 1.0, lx)
+    finally:
+        f.close()
