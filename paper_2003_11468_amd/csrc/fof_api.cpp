@@ -51,7 +51,7 @@ struct Layout {
     int64_t n_cells = 0;
     int64_t scan_tiles = 0;
     int64_t n_tiles = 0;
-    int32_t levels = 2, direct = 0, fused_link = 0;
+    int32_t levels = 2, fused_link = 0;
     int32_t group_parts = 1;
     int64_t group_counts = 1;
     int32_t bucket_shift = 0, n_buckets = 1;
@@ -317,13 +317,12 @@ fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, in
 // Sizes up to which a run is laid out for few launches; each line lies where
 // the two ways measure the same, on uniform and clustered boxes:
 //  one sort level: its tiles take their places by atomics on at most
-//   kWideBuckets counters (14 ns each on one of them);
-//  results straight to input order: scattered writes in outputs that fit the
-//   caches (3e5 particles 9 us against 20 in three launches, 1e6 28 against 27);
+//   kWideBuckets counters (14 ns each on one of them), and the results go
+//   straight to input order, scattered writes in outputs that fit the caches
+//   (3e5 particles 9 us against 20 in three launches, 1e6 28 against 27);
 //  fused link: a wave that merges its own links waits for them (1e5 clustered
 //   particles 41 us against 23 + 14 + 25 in three launches).
 constexpr int64_t kOneLevelMax = 1 << 21;
-constexpr int64_t kDirectMax = 1 << 20;
 constexpr int64_t kFusedLinkMax = 1 << 17;
 
 // Sort levels and the workspace carve-up for n particles in `cells` cells
@@ -366,7 +365,6 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
             p.levels = 1;
         }
         if (p.levels < 2) p.bucket_shift = p.seg_shift;
-        p.direct = n_total <= kDirectMax;
         p.fused_link = n_total <= kFusedLinkMax && !o.collect_stats && o.domains <= 1 && !(o.schedule & (16 | 32));
     }
     if (p.bucket_shift < p.seg_shift) p.bucket_shift = p.seg_shift;
@@ -502,7 +500,6 @@ void carve(const fof_options &o, const Layout &p, const BoxDev &box0, void *ws, 
     d.levels = p.levels;
     d.group_parts = p.group_parts;
     d.group_counts = p.group_counts;
-    d.direct = p.direct;
     d.fused_link = p.fused_link;
     d.bucket_shift = p.bucket_shift;
     d.n_buckets = p.n_buckets;
@@ -548,8 +545,6 @@ void carve(const fof_options &o, const Layout &p, const BoxDev &box0, void *ws, 
     d.seg_end = at<int32_t>(ws, p.o_seg);
     d.staging2 = at<float4>(ws, p.o_staging2);
     d.stage2_k = at<int32_t>(ws, p.o_stage2_k);
-    d.seg_src = p.levels == 2 ? d.staging2 : d.staging;
-    d.seg_k = p.levels == 2 ? d.stage2_k : nullptr;
     d.edge_fill = at<unsigned int>(ws, p.o_edge_fill);
     d.n_waves = (p.n + 63) / 64;
     d.label = nullptr;

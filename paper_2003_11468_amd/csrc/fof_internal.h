@@ -57,10 +57,10 @@ struct Plan {
     int64_t scan_tiles;     // scratch ints for the tile sums of the scans
     int64_t n_tiles;        // input tiles of the bucket pass (2048 particles each)
     int32_t levels;         // levels of the sort above the cells: 2 buckets and segments, 1 segments
-                            // alone (bucket = segment), 0 none (one segment, sorted from the input)
+                            // alone (bucket = segment), 0 none (one segment, sorted from the input);
+                            // below 2 the results are written straight to input order
     int32_t group_parts;    // partial group counts per box, kGroupStride entries apart (1: no stride)
     int64_t group_counts;   // entries of n_groups
-    int32_t direct;         // 1: the results are written straight to input order (no staging slots)
     int32_t fused_link;     // 1: the per-particle search merges its links itself, beside the pre-merge
     int32_t bucket_shift;   // bucket of a cell = cell >> bucket_shift
     int32_t n_buckets;      // at most kMaxBuckets (levels 2) or kWideBuckets (levels 1)
@@ -96,8 +96,6 @@ struct Plan {
     int32_t *stpos;         // [n] staging slot of input particle i
     float4 *staging2;       // [n] segment order (cells of a segment together, unordered inside)
     int32_t *stage2_k;      // [n] staging slot of each segment-order slot
-    const float4 *seg_src;  // the segment order: staging2, or staging when buckets are segments
-    const int32_t *seg_k;   // stage2_k, or null when the staging slot is the segment-order slot
     uint2 *occ;             // [n_segments << (seg_shift - 5) + 2] per 32 cells: .x bit k: cell 32w + k
                             // holds a particle; .y the cstart index of the first occupied cell at or
                             // after cell 32w. Cell c starts at sorted slot

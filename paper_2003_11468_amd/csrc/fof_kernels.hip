@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
         const int b = stage_b[j];
         const int dst = dst0[b] + (j - first[b]);
         p.staging[dst] = e;
-        if (!p.direct) p.stpos[__float_as_int(e.w)] = dst;
+        if constexpr (kPlace == kScan) p.stpos[__float_as_int(e.w)] = dst;
     }
 }
 
@@ -499,12 +499,14 @@ static_assert(kCntCap >= kOrderCap, "a segment placed through LDS is one window"
 // kWordsMax: the occupancy words of the largest segment this instance takes
 // (segments of up to 2^14 cells: one word per thread, the smaller LDS
 // footprint; above: several per thread).
-// kInput: the one segment of a run of at most kOneSegment particles, read from
-// the input itself: this launch is then the whole build (it clears the run's
-// counters and checks the coordinates too).
-template <int kWordsMax, bool kInput>
-__global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(kWordsMax <= 1024 && !kInput ? 8 : 6))) k_cell_sort(Plan p)
+// kLevels 0: the one segment of a run of at most kOneSegment particles, read
+// from the input itself: this launch is then the whole build (it clears the
+// run's counters and checks the coordinates too).
+template <int kWordsMax, int kLevels>
+__global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(kWordsMax <= 1024 ? 8 : 6))) k_cell_sort(Plan p)
 {
+    constexpr bool kInput = kLevels == 0;
+    constexpr bool kStaged = kLevels == 2;   // results go back through staging slots
     BoxHint hint;
     constexpr int kWordsPerThread = (kWordsMax + kSegBlock - 1) / kSegBlock;
     static_assert(kWordsMax % kSegBlock == 0 || kWordsMax < kSegBlock, "whole words per thread");
@@ -527,10 +529,9 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
         if constexpr (kInput) {
             return make_float4(p.pos[3 * k], p.pos[3 * k + 1], p.pos[3 * k + 2], __int_as_float(k));
         } else {
-            return p.seg_src[k];
+            return kStaged ? p.staging2[k] : p.staging[k];
         }
     };
-    auto slot_of = [&](int k) { return p.seg_k ? p.seg_k[k] : k; };   // its staging slot
     const int seg_cells = words << 5;
     // dense slots of a segment placed through LDS (step 5), before its slot order (step 6)
     unsigned long long *dense = reinterpret_cast<unsigned long long *>(order);
@@ -725,7 +726,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                 for (int q = 0; q < kPlaceUnroll; ++q)
                     if (k0 + q * kSegBlock < e) {
                         v[q] = source(k0 + q * kSegBlock);
-                        kk[q] = p.direct ? 0 : slot_of(k0 + q * kSegBlock);
+                        if constexpr (kStaged) kk[q] = p.stage2_k[k0 + q * kSegBlock];
                     }
 #pragma unroll
                 for (int q = 0; q < kPlaceUnroll; ++q) {
@@ -744,7 +745,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                     p.gmin[dst] = i;
                     p.parent[dst] = dst;
                     p.gsize[dst] = 1;
-                    if (!p.direct) p.kmap[dst] = kk[q];
+                    if constexpr (kStaged) p.kmap[dst] = kk[q];
                 }
             }
         }
@@ -770,7 +771,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
             if (d0 + q * kSegBlock < P) {
                 from[q] = a + order[d0 + q * kSegBlock];
                 v[q] = source(from[q]);
-                k_of[q] = p.direct ? 0 : slot_of(from[q]);
+                if constexpr (kStaged) k_of[q] = p.stage2_k[from[q]];
             }
 #pragma unroll
         for (int q = 0; q < kSegUnroll; ++q)
@@ -782,7 +783,7 @@ __global__ void __launch_bounds__(kSegBlock) __attribute__((amdgpu_waves_per_eu(
                 p.gmin[dst] = i;
                 p.parent[dst] = dst;
                 p.gsize[dst] = 1;
-                if (!p.direct) p.kmap[dst] = k_of[q];
+                if constexpr (kStaged) p.kmap[dst] = k_of[q];
             }
     }
 }
@@ -971,7 +972,7 @@ __global__ void __launch_bounds__(kBlock) k_resolve(Plan p)
     resolve_tile(p, xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x);
 }
 
-// Resolve straight into input order (Plan::direct): while the outputs fit in
+// Resolve straight into input order (fewer than two sort levels): while the outputs fit in
 // the caches the scattered 4-byte writes cost less than staging slots, their
 // two maps in the sort, a group count and a gather, each a launch. A
 // persistent grid, so that each box's count takes few atomics.
@@ -1101,7 +1102,10 @@ __global__ void k_clear_ints(int *a, int n)
 // ascending): a group appears once, at the particle whose index is its label,
 // the only one with a non-zero size. Per tile of kSortTile particles: count,
 // then an exclusive prefix over the tiles, then each tile writes its groups
-// in order (thread t owns kSortItems consecutive particles).
+// in order (thread t owns kSortItems consecutive particles). Up to
+// kCatSumTiles tiles each tile sums the counts before it itself (at most 32 KB
+// out of the caches), so the whole is two launches instead of four.
+constexpr int64_t kCatSumTiles = 8192;
 
 __global__ void __launch_bounds__(kBlock) k_cat_count(const Plan p, const int32_t *size, int min_size, int *tile_count)
 {
@@ -1115,8 +1119,9 @@ __global__ void __launch_bounds__(kBlock) k_cat_count(const Plan p, const int32_
     if (threadIdx.x == 0) tile_count[blockIdx.x] = total;
 }
 
+template <bool kSum>
 __global__ void __launch_bounds__(kBlock) k_cat_write(const Plan p, const int32_t *label, const int32_t *size,
-                                                      int min_size, const int *tile_off, int32_t *g_first,
+                                                      int min_size, int *tile_off, int32_t *g_first,
                                                       int32_t *g_size, int32_t *g_box, int64_t capacity)
 {
     __shared__ int lds[kBlock / 64];
@@ -1129,7 +1134,17 @@ __global__ void __launch_bounds__(kBlock) k_cat_write(const Plan p, const int32_
         c += take[k] ? 1 : 0;
     }
     int total;
-    int64_t at = (int64_t)tile_off[blockIdx.x] + block_excl_scan<kBlock>(c, lds, &total);
+    const int rank = block_excl_scan<kBlock>(c, lds, &total);
+    int before;
+    if constexpr (kSum) {
+        int sum = 0;
+        for (int t = threadIdx.x; t < (int)blockIdx.x; t += kBlock) sum += tile_off[t];
+        block_excl_scan<kBlock>(sum, lds, &before);
+        if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) tile_off[gridDim.x] = before + total;
+    } else {
+        before = tile_off[blockIdx.x];
+    }
+    int64_t at = (int64_t)before + rank;
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k)
         if (take[k]) {
@@ -1212,7 +1227,7 @@ hipError_t launch_build(const Plan &p, hipStream_t stream, KernelTimer *t)
     }
     const dim3 grid((unsigned)p.n_segments), block(kSegBlock);
     if (p.levels == 0 && p.n > 0) {
-        hipLaunchKernelGGL((k_cell_sort<(1 << kSegLog2Max) / 32, true>), grid, block, 0, stream, p);
+        hipLaunchKernelGGL((k_cell_sort<(1 << kSegLog2Max) / 32, 0>), grid, block, 0, stream, p);
         return hipGetLastError();
     }
     const unsigned seg_tiles = xcd_grid(p.n_tiles + p.n_buckets);
@@ -1238,13 +1253,13 @@ hipError_t launch_build(const Plan &p, hipStream_t stream, KernelTimer *t)
         FOF_TIMED(K_SEG_SCAN, scan_exclusive(p.seg_end, p.n_segments, p.scan_part, stream));
     if (p.levels == 2 && p.n > 0)
         FOF_TIMED(K_SEG_SCATTER, hipLaunchKernelGGL(k_seg_scatter, dim3(seg_tiles), dim3(kBlock), 0, stream, p));
-    if (p.seg_shift <= 14)
-        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL((k_cell_sort<(1 << 14) / 32, false>), grid, block, 0, stream, p));
+    auto sort = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, p); };
+    constexpr int kSmall = (1 << 14) / 32, kMiddle = (1 << 15) / 32, kLarge = (1 << kSegLog2Max) / 32;
+    const bool one = p.levels == 1;
+    if (p.seg_shift <= 14) FOF_TIMED(K_CELL_SORT, one ? sort(k_cell_sort<kSmall, 1>) : sort(k_cell_sort<kSmall, 2>));
     else if (p.seg_shift == 15)
-        FOF_TIMED(K_CELL_SORT, hipLaunchKernelGGL((k_cell_sort<(1 << 15) / 32, false>), grid, block, 0, stream, p));
-    else
-        FOF_TIMED(K_CELL_SORT,
-                  hipLaunchKernelGGL((k_cell_sort<(1 << kSegLog2Max) / 32, false>), grid, block, 0, stream, p));
+        FOF_TIMED(K_CELL_SORT, one ? sort(k_cell_sort<kMiddle, 1>) : sort(k_cell_sort<kMiddle, 2>));
+    else FOF_TIMED(K_CELL_SORT, one ? sort(k_cell_sort<kLarge, 1>) : sort(k_cell_sort<kLarge, 2>));
     return hipGetLastError();
 }
 
@@ -1255,11 +1270,17 @@ hipError_t launch_catalogue(const Plan &p, const int32_t *label, const int32_t *
     // exclusive prefix over n_tiles + 1 entries leaves the total in the last
     int *count = p.bucket_hist;
     const unsigned tiles = (unsigned)p.n_tiles;
+    if (tiles && p.n_tiles <= kCatSumTiles) {   // the last tile leaves the total
+        hipLaunchKernelGGL(k_cat_count, dim3(tiles), dim3(kBlock), 0, stream, p, size, min_size, count);
+        hipLaunchKernelGGL(k_cat_write<true>, dim3(tiles), dim3(kBlock), 0, stream, p, label, size, min_size, count,
+                           g_first, g_size, g_box, capacity);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_clear_ints, dim3(1), dim3(kBlock), 0, stream, count + p.n_tiles, 1);
     if (tiles) hipLaunchKernelGGL(k_cat_count, dim3(tiles), dim3(kBlock), 0, stream, p, size, min_size, count);
     scan_exclusive(count, p.n_tiles + 1, p.scan_part, stream);
     if (tiles)
-        hipLaunchKernelGGL(k_cat_write, dim3(tiles), dim3(kBlock), 0, stream, p, label, size, min_size, count,
+        hipLaunchKernelGGL(k_cat_write<false>, dim3(tiles), dim3(kBlock), 0, stream, p, label, size, min_size, count,
                            g_first, g_size, g_box, capacity);
     return hipGetLastError();
 }
@@ -1280,7 +1301,7 @@ hipError_t launch_finalize(const Plan &p, hipStream_t stream, KernelTimer *t)
     const unsigned flatten_grid = (unsigned)min(kStreamBlocks, grid_tiles(p.n));
     if (p.stats) hipLaunchKernelGGL(k_find_depth, dim3(flatten_grid), dim3(kBlock), 0, stream, p);
     FOF_TIMED(K_FLATTEN, hipLaunchKernelGGL(k_flatten, dim3(flatten_grid), dim3(kBlock), 0, stream, p));
-    if (p.direct) {
+    if (p.levels < 2) {
         int64_t g = (p.n + kBlock - 1) / kBlock;
         if (g > kDirectBlocks) g = kDirectBlocks;
         hipLaunchKernelGGL(k_resolve_direct, dim3(xcd_grid(g)), dim3(kBlock), 0, stream, p);
