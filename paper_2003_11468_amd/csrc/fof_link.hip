@@ -293,8 +293,7 @@ struct EdgeSink {
 constexpr int kMaxUnits = 64 * kMaxRanges;
 
 struct SparseLds {
-    int start[kMaxUnits + 1];   // first pair of each unit (exclusive prefix)
-    int j0[kMaxUnits];          // first candidate of each unit
+    int2 unit[kMaxUnits + 1];   // {first pair of the unit (exclusive prefix), its first candidate}
     unsigned short tag[kMaxUnits];   // shift code (bits 0-5) | home lane << 8
     float4 home[64];                 // the home particles
     int2 ebuf[kEdgeBuf];             // edge sink buffer
@@ -326,13 +325,12 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
     const int q0 = (int)(((int64_t)n_pairs * lane) >> 6);
     const int q1 = (int)(((int64_t)n_pairs * (lane + 1)) >> 6);
     int u = 0;
-#pragma unroll
-    for (int step = 512; step > 0; step >>= 1) {
+    for (int step = n_units > 1 ? 1 << (31 - __clz(n_units - 1)) : 0; step > 0; step >>= 1) {
         const int nxt = u + step;
-        if (nxt < n_units && L.start[nxt] <= q0) u = nxt;
+        if (nxt < n_units && L.unit[nxt].x <= q0) u = nxt;
     }
-    int next_start = L.start[u + 1];
-    int jq = L.j0[u] + (q0 - L.start[u]);   // candidate of pair q
+    int next_start = L.unit[u + 1].x;
+    int jq = L.unit[u].y + (q0 - L.unit[u].x);   // candidate of pair q
     int tag = L.tag[u];
     float4 h = L.home[tag >> 8];
     // four steps at a time: their candidate loads are in flight together
@@ -348,8 +346,8 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
             lv[a] = q < q1 && k + a < steps;
             if (lv[a] && q == next_start) {   // the next unit starts here
                 ++u;
-                next_start = L.start[u + 1];
-                jq = L.j0[u];
+                next_start = L.unit[u + 1].x;
+                jq = L.unit[u].y;
                 tag = L.tag[u];
                 h = L.home[tag >> 8];
             }
@@ -462,6 +460,7 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
         Span R[kMaxRanges];   // own cell, next cell, then two per neighbour row
         float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
         int b = 0;
+        bool simple = true;
         if (s64 < p.n) {
             const int s = (int)s64;
             b = p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, s64, hint);
@@ -475,7 +474,6 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
             const int *cst = p.cstart;
             const int dense_min = p.dense_min;
             const int seg_shift = p.seg_shift;
-            const int64_t rb0 = c - cx;
             // Boundaries of the own row and the four neighbour rows (dy, dz) =
             // (1, 0), (-1, 1), (0, 1), (1, 1): with the own cell these hold the
             // 13 half-shell cells. Occupancy words (bits and rank base per 32
@@ -498,7 +496,7 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
             const int nxp = cx + 1 < nc ? cx + 1 : 0;
             const bool inner = cx >= 1 && cx + 1 < nc;
             const int rdy[4] = {1, -1, 0, 1}, rdz[4] = {0, 1, 1, 1};
-            int64_t rb[4], c0[4];
+            int64_t c0[4];
             int yz[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -507,8 +505,7 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
                 else if (ny < 0) { ny += nc; code |= 1 << 2; }
                 if (nz >= nc) { nz -= nc; code |= 2 << 4; }
                 yz[r] = code;
-                rb[r] = bd.cell_base + ((int64_t)nz * nc + ny) * nc;
-                c0[r] = rb[r] + (inner ? cx - 1 : 0);
+                c0[r] = bd.cell_base + ((int64_t)nz * nc + ny) * nc + (inner ? cx - 1 : 0);
             }
             // Two rounds of loads, each issued whole before any of its results
             // is used, with no branch among them: first the occupancy words of
@@ -531,96 +528,112 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
                 qr[r] = *reinterpret_cast<const int4a4 *>(cst + rank_in(wr[r].x, wr[r].y, c0[r]));
             }
             const int own_start = qo.x, own_end = qo.y;
-            int nxt_start = 0, nxt_end = 0;
-            if (nxp && ((c ^ (c + 1)) >> seg_shift) == 0) {
-                // the next cell in the same segment: its entries follow the own cell's
+            // The plain case: no row wraps at an x face or crosses a segment,
+            // so its cells follow each other and their bounds are in the 16
+            // bytes already loaded: one range per row, two around a dense
+            // middle cell. What it leaves out is most of a tile's setup, which
+            // is bound by instruction issue.
+            const bool searches = own_end - own_start < dense_min;   // dense cells are searched elsewhere
+            simple = inner && !p.sample && ((c ^ (c + 1)) >> seg_shift) == 0;
+            {
                 const unsigned b1 = (unsigned)(c + 1) & 31u;
-                const unsigned nbits = b1 ? wo.x : wo.z;
-                if ((nbits >> b1) & 1u) {
-                    nxt_start = qo.y;
-                    nxt_end = qo.z;
-                }
-            } else {
-                span(rb0 + nxp, nxt_start, nxt_end);
+                const bool nxt = (((b1 ? wo.x : wo.z) >> b1) & 1u) && qo.z - qo.y < dense_min;
+                R[0] = Span{s + 1, searches ? (nxt ? qo.z : qo.y) : 0, 0};
             }
-            int st[4][3], en[4][3];
+            bool crowded = false;   // some row may hold a dense cell
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+                const int4a4 q = qr[r];
+                const unsigned occupied = __popc(mr[r]);
+                const int end = occupied == 0 ? q.x : (occupied == 1 ? q.y : (occupied == 2 ? q.z : q.w));
+                simple = simple && ((c0[r] ^ (c0[r] + 2)) >> seg_shift) == 0;
+                crowded = crowded || end - q.x >= dense_min;
+                R[2 + 2 * r] = Span{q.x, searches ? end : 0, yz[r]};
+            }
+            simple = simple || !searches;
+            if (__ballot(crowded && searches && simple)) {
 #pragma unroll
-                for (int e = 0; e < 3; ++e) st[r][e] = en[r][e] = 0;
-                const unsigned m = mr[r];
-                if (inner && ((c0[r] ^ (c0[r] + 2)) >> seg_shift) == 0) {
-                    // the three cells in one segment: their occupied cells have
-                    // consecutive entries, so the 16-byte read holds every boundary
+                for (int r = 0; r < 4; ++r) {
                     const int4a4 q = qr[r];
-                    auto pick = [&](unsigned k) { return k == 0 ? q.x : (k == 1 ? q.y : (k == 2 ? q.z : q.w)); };
-                    const unsigned o1 = m & 1u, o2 = o1 + ((m >> 1) & 1u), o3 = o2 + (m >> 2);
-                    const int b1 = pick(o1), b2 = pick(o2);
-                    st[r][0] = q.x; en[r][0] = b1;
-                    st[r][1] = b1; en[r][1] = b2;
-                    st[r][2] = b2; en[r][2] = pick(o3);
-                } else if (inner) {
-                    if (m) {
+                    const unsigned o1 = mr[r] & 1u, o2 = o1 + ((mr[r] >> 1) & 1u);
+                    const int b1 = o1 ? q.y : q.x, b2 = o2 == 0 ? q.x : (o2 == 1 ? q.y : q.z);
+                    const int b3 = R[2 + 2 * r].j1;   // below the row's start for a lane that does not search
+                    const bool d0 = b1 - q.x >= dense_min, d1 = b2 - b1 >= dense_min, d2 = b3 - b2 >= dense_min;
+                    const int end = d2 ? b2 : b3;
+                    R[2 + 2 * r].j0 = d0 ? b1 : q.x;
+                    R[2 + 2 * r].j1 = d1 ? min(b1, b3) : end;
+                    R[3 + 2 * r] = Span{b2, d1 ? end : 0, yz[r]};
+                }
+            }
+            // Lanes at an x face, of a row across segments, or of the first
+            // pass of the giant-component skip (centre cells of the axis
+            // neighbours (dy, dz) = (1, 0) and (0, 1) only): cell by cell.
+            if (!simple) {
+                int st[3], en[3];
+                st[0] = en[0] = 0;
+                span(c - cx + nxp, st[0], en[0]);
+                R[0] = Span{s + 1, own_end, 0};
+                R[1] = en[0] - st[0] < dense_min ? Span{st[0], en[0], cx + 1 < nc ? 0 : 2} : Span{};
+                const int xcode[3] = {cx == 0 ? 1 : 0, 0, cx + 1 == nc ? 2 : 0};
 #pragma unroll
-                        for (int e = 0; e < 3; ++e) span(c0[r] + e, st[r][e], en[r][e]);
-                    }
-                } else {
+                for (int r = 0; r < 4; ++r) {
+                    int ny = cy + rdy[r], nz = cz + rdz[r];
+                    ny += ny >= nc ? -nc : (ny < 0 ? nc : 0);
+                    nz += nz >= nc ? -nc : 0;
+                    const int64_t row = bd.cell_base + ((int64_t)nz * nc + ny) * nc;
 #pragma unroll
                     for (int e = 0; e < 3; ++e) {
                         int nx = cx - 1 + e;
                         nx += nx < 0 ? nc : (nx >= nc ? -nc : 0);
-                        span(rb[r] + nx, st[r][e], en[r][e]);
+                        st[e] = en[e] = 0;
+                        if (!p.sample || ((r == 0 || r == 2) && e == 1)) span(row + nx, st[e], en[e]);
                     }
-                }
-            }
-            if (own_end - own_start < dense_min) {
-                // own cell above s, then cell cx + 1 (across the high x face when cx is the top cell)
-                const int xcode_next = cx + 1 < nc ? 0 : 2;
-                if (nxt_end - nxt_start < dense_min && xcode_next == 0 && nxt_start == own_end) {
-                    R[0] = Span{s + 1, nxt_end, 0};
-                } else {
-                    R[0] = Span{s + 1, own_end, 0};
-                    if (nxt_end - nxt_start < dense_min) R[1] = Span{nxt_start, nxt_end, xcode_next};
-                }
-                const int xcode[3] = {cx == 0 ? 1 : 0, 0, cx + 1 == nc ? 2 : 0};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (p.sample) {
-                        // the first pass of the giant-component skip: the axis
-                        // neighbours (dy, dz) = (1, 0) and (0, 1), centre cells only
-#pragma unroll
-                        for (int e = 0; e < 3; ++e)
-                            if (!((r == 0 || r == 2) && e == 1)) en[r][e] = st[r][e];
-                    }
-                    row_spans(st[r], en[r], xcode, yz[r], dense_min, R[2 + 2 * r], R[3 + 2 * r]);
+                    const int code = R[2 + 2 * r].code;
+                    R[2 + 2 * r] = R[3 + 2 * r] = Span{};
+                    row_spans(st, en, xcode, code, dense_min, R[2 + 2 * r], R[3 + 2 * r]);
                 }
             }
         }
         // flatten the units of the wave: unit and pair offsets by prefix sums
-        int my_pairs = 0, my_units = 0;
+        // (mostly every other range is empty in all lanes)
+        bool more = false;
 #pragma unroll
-        for (int r = 0; r < kMaxRanges; ++r)
-            if (R[r].j1 > R[r].j0) {
-                my_pairs += R[r].j1 - R[r].j0;
-                ++my_units;
-            }
+        for (int r = 1; r < kMaxRanges; r += 2) more = more || R[r].j1 > R[r].j0;
+        const bool all_simple = __ballot(more) == 0;
+        int my_pairs = 0, my_units = 0;
+        auto add_up = [&](const Span &x) {
+            const int len = max(x.j1 - x.j0, 0);
+            my_pairs += len;
+            my_units += len > 0 ? 1 : 0;
+        };
+#pragma unroll
+        for (int r = 0; r < kMaxRanges; r += 2) add_up(R[r]);
+        if (!all_simple) {
+#pragma unroll
+            for (int r = 1; r < kMaxRanges; r += 2) add_up(R[r]);
+        }
         const int unit_incl = wave_incl_scan(my_units);
         const int pair_incl = wave_incl_scan(my_pairs);
-        const int n_units = __shfl(unit_incl, 63, 64);
-        const int n_pairs = __shfl(pair_incl, 63, 64);
+        const int n_units = __builtin_amdgcn_readlane(unit_incl, 63);
+        const int n_pairs = __builtin_amdgcn_readlane(pair_incl, 63);
         if (n_pairs == 0) continue;
         {
             int u = unit_incl - my_units, pr = pair_incl - my_pairs;
-#pragma unroll
-            for (int r = 0; r < kMaxRanges; ++r)
-                if (R[r].j1 > R[r].j0) {
-                    L.start[u] = pr;
-                    L.j0[u] = R[r].j0;
-                    L.tag[u] = R[r].code | (lane << 8);
-                    pr += R[r].j1 - R[r].j0;
+            auto put = [&](const Span &x) {
+                if (x.j1 > x.j0) {
+                    L.unit[u] = make_int2(pr, x.j0);
+                    L.tag[u] = x.code | (lane << 8);
+                    pr += x.j1 - x.j0;
                     ++u;
                 }
-            if (lane == 63) L.start[n_units] = n_pairs;
+            };
+#pragma unroll
+            for (int r = 0; r < kMaxRanges; r += 2) put(R[r]);
+            if (!all_simple) {
+#pragma unroll
+                for (int r = 1; r < kMaxRanges; r += 2) put(R[r]);
+            }
+            if (lane == 63) L.unit[n_units].x = n_pairs;
             L.home[lane] = pi;
         }
         __builtin_amdgcn_wave_barrier();
@@ -681,7 +694,7 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
 }
 
 template <bool kFP64, bool kStats>
-__global__ void __launch_bounds__(kBlock) k_link_sparse(Plan p)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_link_sparse(Plan p)
 {
     __shared__ SparseLds lds[kWaves];
     sparse_search<kFP64, kStats, false>(p, lds[threadIdx.x >> 6], blockIdx.x, gridDim.x);
@@ -1636,7 +1649,7 @@ __global__ void __launch_bounds__(kBlock) k_dense_premerge(Plan p)
 // links, and the pre-merge side by side in one launch (they touch disjoint
 // sets of particles) instead of three. The first `search` work-groups search.
 template <bool kFP64>
-__global__ void __launch_bounds__(kBlock) k_link_small(Plan p, int search)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_link_small(Plan p, int search)
 {
     union Lds {
         SparseLds sparse[kWaves];
