@@ -28,7 +28,8 @@
  * Conventions
  *  - All device pointers are HIP device memory on the context's device. The
  *    caller owns the positions, the outputs and the workspace; the library
- *    owns only the context and two small pinned staging buffers.
+ *    owns only the context and small pinned host buffers (two for
+ *    staging, one for reading back).
  *  - build/link/finalize enqueue work on the context's stream and return
  *    without waiting, except where a host output pointer is given. A
  *    multi-box build (or relink) copies its box table to the workspace through
@@ -320,7 +321,7 @@ fof_status fof_get_kernel_times(fof_ctx *ctx, double *h_ms, int32_t *h_launches,
 /* Name of kernel k of fof_get_kernel_times ("?" when out of range). */
 const char *fof_kernel_name(int32_t k);
 
-/* Releases the context, its graph and its pinned staging buffer (not the
+/* Releases the context, its graph and its pinned buffers (not the
  * caller's workspace). Waits for the stream. NULL is accepted. */
 fof_status fof_destroy(fof_ctx *ctx);
 

@@ -80,7 +80,7 @@ def load_library():
         raise ImportError(f"{LIB_PATH} is missing: run paper_2003_11468_amd/build.py (hipcc, gfx950)")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
-    i64p, f64p = ctypes.POINTER(i64), ctypes.POINTER(ctypes.c_double)
+    i64p = f64p = vp   # host arrays go as addresses
     sig = {
         "fof_default_options": (None, [ctypes.POINTER(Options)]),
         "fof_create": (ctypes.c_int, [ctypes.POINTER(vp), ctypes.POINTER(Options), vp]),
@@ -122,15 +122,29 @@ def _arr(a, dtype):
     return np.ascontiguousarray(a, dtype=dtype)
 
 
-def _p(a, ctype):
-    return a.ctypes.data_as(ctypes.POINTER(ctype))
+def _p(a) -> int:
+    """Address of a contiguous array that the caller keeps alive over the call."""
+    return a.__array_interface__["data"][0]
+
+
+_I64, _F64 = np.dtype(np.int64), np.dtype(np.float64)
+
+
+def _per_box(v, n):
+    if type(v) is np.ndarray and v.dtype == _F64 and v.shape == (n,) and v.flags.c_contiguous:
+        return v
+    return _arr(np.broadcast_to(np.asarray(v, dtype=np.float64), (n,)), np.float64)
 
 
 def _boxes(offsets, box, lx):
-    off = _arr(offsets, np.int64)
-    L = _arr(np.broadcast_to(np.asarray(box, dtype=np.float64), (len(off) - 1,)), np.float64)
-    l = _arr(np.broadcast_to(np.asarray(lx, dtype=np.float64), (len(off) - 1,)), np.float64)
-    return off, L, l
+    """Offsets, sides and linking lengths as the library takes them. Arrays
+    that are so already pass through: calls on small boxes spend as long on
+    their arguments as on the GPU."""
+    off = offsets
+    if not (type(off) is np.ndarray and off.dtype == _I64 and off.ndim == 1 and off.flags.c_contiguous):
+        off = _arr(offsets, np.int64)
+    n = len(off) - 1
+    return off, _per_box(box, n), _per_box(lx, n)
 
 
 def _dptr(t) -> int:
@@ -159,8 +173,7 @@ def fof_set_stream(ctx, stream: int):
 def fof_workspace_bytes(ctx, offsets, box, lx) -> int:
     off, L, l = _boxes(offsets, box, lx)
     out = ctypes.c_size_t()
-    _check(load_library().fof_workspace_bytes(ctx, _p(off, ctypes.c_int64), _p(L, ctypes.c_double),
-                                              _p(l, ctypes.c_double), len(L), ctypes.byref(out)),
+    _check(load_library().fof_workspace_bytes(ctx, _p(off), _p(L), _p(l), len(L), ctypes.byref(out)),
            "fof_workspace_bytes")
     return int(out.value)
 
@@ -173,9 +186,7 @@ def fof_set_workspace(ctx, ws, nbytes: int | None = None):
 
 def fof_build_cells(ctx, pos, offsets, box, lx):
     off, L, l = _boxes(offsets, box, lx)
-    _check(load_library().fof_build_cells(ctx, ctypes.c_void_p(_dptr(pos)), _p(off, ctypes.c_int64),
-                                          _p(L, ctypes.c_double), _p(l, ctypes.c_double), len(L)),
-           "fof_build_cells")
+    _check(load_library().fof_build_cells(ctx, _dptr(pos), _p(off), _p(L), _p(l), len(L)), "fof_build_cells")
 
 
 def fof_link(ctx):
@@ -188,15 +199,14 @@ def fof_finalize(ctx, group_index, group_size, n_boxes: int | None = None):
     ptr = None
     if n_boxes is not None:
         out = np.zeros(n_boxes, dtype=np.int64)
-        ptr = _p(out, ctypes.c_int64)
-    _check(load_library().fof_finalize(ctx, ctypes.c_void_p(_dptr(group_index)),
-                                       ctypes.c_void_p(_dptr(group_size)), ptr), "fof_finalize")
+        ptr = _p(out)
+    _check(load_library().fof_finalize(ctx, _dptr(group_index), _dptr(group_size), ptr), "fof_finalize")
     return out
 
 
 def fof_read_n_groups(ctx, n_boxes: int) -> np.ndarray:
     out = np.zeros(n_boxes, dtype=np.int64)
-    _check(load_library().fof_read_n_groups(ctx, _p(out, ctypes.c_int64)), "fof_read_n_groups")
+    _check(load_library().fof_read_n_groups(ctx, _p(out)), "fof_read_n_groups")
     return out
 
 
@@ -208,10 +218,8 @@ def fof_get_stats(ctx) -> dict:
 
 def fof_graph_capture(ctx, pos, offsets, box, lx, group_index, group_size):
     off, L, l = _boxes(offsets, box, lx)
-    _check(load_library().fof_graph_capture(ctx, ctypes.c_void_p(_dptr(pos)), _p(off, ctypes.c_int64),
-                                            _p(L, ctypes.c_double), _p(l, ctypes.c_double), len(L),
-                                            ctypes.c_void_p(_dptr(group_index)),
-                                            ctypes.c_void_p(_dptr(group_size))), "fof_graph_capture")
+    _check(load_library().fof_graph_capture(ctx, _dptr(pos), _p(off), _p(L), _p(l), len(L), _dptr(group_index),
+                                            _dptr(group_size)), "fof_graph_capture")
 
 
 def fof_graph_launch(ctx):
@@ -229,8 +237,8 @@ def fof_get_kernel_times(ctx) -> dict:
     ms = np.zeros(cap, dtype=np.float64)
     cnt = np.zeros(cap, dtype=np.int32)
     nk = ctypes.c_int32()
-    _check(load_library().fof_get_kernel_times(ctx, _p(ms, ctypes.c_double), _p(cnt, ctypes.c_int32), cap,
-                                               ctypes.byref(nk)), "fof_get_kernel_times")
+    _check(load_library().fof_get_kernel_times(ctx, _p(ms), cnt.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
+                                               cap, ctypes.byref(nk)), "fof_get_kernel_times")
     lib = load_library()
     return {lib.fof_kernel_name(k).decode(): (float(ms[k]), int(cnt[k])) for k in range(nk.value)}
 
@@ -253,9 +261,8 @@ def fof_catalogue(ctx, label, size, min_size: int, first=None, gsize=None, gbox=
 
 def fof_relink(ctx, lx, n_boxes: int):
     """New linking lengths (one per box, each at most the build's) over the built cells."""
-    l = _arr(np.broadcast_to(np.asarray(lx, dtype=np.float64), (int(n_boxes),)), np.float64)
-    _check(load_library().fof_relink(ctx, l.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), int(n_boxes)),
-           "fof_relink")
+    l = _per_box(lx, int(n_boxes))
+    _check(load_library().fof_relink(ctx, _p(l), int(n_boxes)), "fof_relink")
 
 
 def fof_label_noalloc(pos, box, lx, group_index, group_size, opt: Options | None = None, stream: int | None = None,
@@ -355,11 +362,13 @@ class FoF:
 
     def run(self, pos, offsets, box, lx, label=None, size=None, sync: bool = True):
         """build + link + finalize. Returns (label, size, n_groups or None)."""
+        offsets, box, lx = _boxes(offsets, box, lx)
         self._check_pos(pos, offsets)
         self.reserve(offsets, box, lx)
+        n = pos.shape[0]
         if label is None or size is None:
-            label, size = self.outputs(pos.shape[0])
-        self._n = pos.shape[0]
+            label, size = self.outputs(n)
+        self._n = n
         fof_build_cells(self.ctx, pos, offsets, box, lx)
         fof_link(self.ctx)
         ng = fof_finalize(self.ctx, label, size, len(offsets) - 1 if sync else None)

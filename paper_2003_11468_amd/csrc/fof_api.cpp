@@ -148,6 +148,14 @@ struct fof_ctx {
     bool stage_pending[2] = {false, false};
     int stage_next = 0;
 
+    // Host memory for what is read back: pinned from the second read on, and
+    // grown when a larger one comes. A copy into pageable memory makes the
+    // runtime wait and copy again, 10 us, 23 with seven launches before it; a
+    // context that reads once saves the allocation instead, which costs more.
+    char *read_buf = nullptr;
+    size_t read_bytes = 0;
+    std::vector<char> first_read;
+
     int state = 0;             // 0 idle, 1 cells built, 2 linked
     bool cells_valid = false;  // the last build's cells and sorted positions are in the workspace
     Plan dev{};                // pointers of the current run
@@ -649,19 +657,43 @@ fof_status enqueue_build(fof_ctx *c, hipStream_t s)
     return dev_err(fof::launch_build(c->dev, s, c->timer));
 }
 
+// Copies `bytes` bytes at d_src to the context's read buffer, in stream order,
+// and waits for them.
+fof_status read_device(fof_ctx *c, const void *d_src, size_t bytes, const char **out)
+{
+    char *to = c->read_buf;
+    if (c->first_read.empty()) {
+        c->first_read.resize(bytes);
+        to = c->first_read.data();
+    } else if (c->read_bytes < bytes) {
+        if (c->read_buf) (void)hipHostFree(c->read_buf);
+        c->read_buf = nullptr;
+        c->read_bytes = 0;
+        void *buf = nullptr;
+        if (hipHostMalloc(&buf, bytes, hipHostMallocDefault) != hipSuccess) return FOF_ERR_DEVICE;
+        c->read_buf = to = static_cast<char *>(buf);
+        c->read_bytes = bytes;
+    }
+    if (hipMemcpyAsync(to, d_src, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+        return FOF_ERR_DEVICE;
+    if (hipStreamSynchronize(c->stream) != hipSuccess) return FOF_ERR_DEVICE;
+    *out = to;
+    return FOF_OK;
+}
+
 fof_status read_back(fof_ctx *c, int64_t *h_n_groups, Counters *h_counters)
 {
     const HostPlan &p = c->plan;
     // the counters and, behind them in the workspace, the group counts: one copy
     const size_t bytes = (p.o_groups - p.o_counters) + sizeof(unsigned long long) * (size_t)p.group_counts;
-    std::vector<char> buf(bytes);
-    if (hipMemcpyAsync(buf.data(), c->dev.counters, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-        return FOF_ERR_DEVICE;
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return FOF_ERR_DEVICE;
+    const char *buf = nullptr;
+    const fof_status st = read_device(c, c->dev.counters, bytes, &buf);
+    if (st != FOF_OK) return st;
     Counters cnt;
-    std::memcpy(&cnt, buf.data(), sizeof(cnt));
+    std::memcpy(&cnt, buf, sizeof(cnt));
     if (h_n_groups)
-        for (int32_t k = 0; k < p.n_boxes; ++k) h_n_groups[k] = fof::groups_of_box(buf.data() + (p.o_groups - p.o_counters), c->dev, k);
+        for (int32_t k = 0; k < p.n_boxes; ++k)
+            h_n_groups[k] = fof::groups_of_box(buf + (p.o_groups - p.o_counters), c->dev, k);
     if (h_counters) *h_counters = cnt;
     if (cnt.error & 2u) return FOF_ERR_DEVICE;   // a device-side consistency check failed
     return (cnt.error & 1u) ? FOF_ERR_OUT_OF_BOX : FOF_OK;
@@ -848,12 +880,10 @@ fof_status fof_catalogue(fof_ctx *ctx, const int32_t *d_group_index, const int32
     fof_status st = dev_err(fof::launch_catalogue(p, d_group_index, d_group_size, min_size, d_first, d_size, d_box,
                                                   capacity, ctx->stream));
     if (st != FOF_OK) return st;
-    int total = 0;
-    if (hipMemcpyAsync(&total, p.bucket_hist + p.n_tiles, sizeof(int), hipMemcpyDeviceToHost, ctx->stream) !=
-        hipSuccess)
-        return FOF_ERR_DEVICE;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return FOF_ERR_DEVICE;
-    *h_count = total;
+    const char *total = nullptr;
+    st = read_device(ctx, p.bucket_hist + p.n_tiles, sizeof(int), &total);
+    if (st != FOF_OK) return st;
+    *h_count = *reinterpret_cast<const int *>(total);
     return FOF_OK;
 }
 
@@ -961,6 +991,7 @@ fof_status fof_destroy(fof_ctx *ctx)
         if (ctx->stage[k]) (void)hipHostFree(ctx->stage[k]);
         if (ctx->stage_done[k]) (void)hipEventDestroy(ctx->stage_done[k]);
     }
+    if (ctx->read_buf) (void)hipHostFree(ctx->read_buf);
     delete ctx->timer;
     delete ctx;
     return FOF_OK;
