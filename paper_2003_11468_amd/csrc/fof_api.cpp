@@ -327,10 +327,12 @@ fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, in
 //  one sort level: its tiles take their places by atomics on at most
 //   kWideBuckets counters (14 ns each on one of them), and the results go
 //   straight to input order, scattered writes in outputs that fit the caches
-//   (3e5 particles 9 us against 20 in three launches, 1e6 28 against 27);
+//   (3e5 particles 9 us against 20 in three launches, 1e6 28 against 27); with
+//   2048 buckets, 8e5 particles take 154 us this way and 163 in two levels,
+//   1e6 185 and 176, so more than kWideBuckets do not pay;
 //  fused link: a wave that merges its own links waits for them (1e5 clustered
 //   particles 41 us against 23 + 14 + 25 in three launches).
-constexpr int64_t kOneLevelMax = 1 << 21;
+constexpr int64_t kOneLevelMax = 900000;
 constexpr int64_t kFusedLinkMax = 1 << 17;
 
 // Sort levels and the workspace carve-up for n particles in `cells` cells
