@@ -295,8 +295,9 @@ struct EdgeSink {
 constexpr int kMaxUnits = 64 * kMaxRanges;
 
 struct SparseLds {
-    int2 unit[kMaxUnits + 1];   // {first pair of the unit (exclusive prefix), its first candidate}
-    unsigned short tag[kMaxUnits];   // shift code (bits 0-5) | home lane << 8
+    // one entry past the last unit holds the number of pairs, and one more is read ahead
+    int2 unit[kMaxUnits + 2];   // {first pair of the unit (exclusive prefix), its first candidate}
+    unsigned short tag[kMaxUnits + 2];   // shift code (bits 0-5) | home lane << 8
     float4 home[64];                 // the home particles
     int2 ebuf[kEdgeBuf];             // edge sink buffer
     unsigned long long adj[64];      // links inside the tile: bit v of adj[u] for home u, slot s0 + v
@@ -331,13 +332,17 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
         const int nxt = u + step;
         if (nxt < n_units && L.unit[nxt].x <= q0) u = nxt;
     }
-    int next_start = L.unit[u + 1].x;
     int jq = L.unit[u].y + (q0 - L.unit[u].x);   // candidate of pair q
-    int tag = L.tag[u];
-    float4 h = L.home[tag >> 8];
-    // four steps at a time: their candidate loads are in flight together
+    int tag = L.tag[u], next_start = L.unit[u + 1].x;
+    // the unit after this one, read ahead, so that a lane that steps into it
+    // does not wait for LDS
+    int ahead_j0 = L.unit[u + 1].y, ahead_next = L.unit[u + 2].x, ahead_tag = L.tag[u + 1];
+    u += 2;
+    // four steps at a time: their candidate loads are in flight together, and
+    // their home particles are read while those are (lanes past their last
+    // pair load their tile's first particle)
     constexpr int kAhead = 4;
-    const int steps = (n_pairs + 63) >> 6;
+    const int steps = (n_pairs + 63) >> 6;   // at least every lane's pairs
     int q = q0;
     for (int k = 0; k < steps; k += kAhead) {
         int jj[kAhead], tg[kAhead];
@@ -345,25 +350,26 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
         bool lv[kAhead];
 #pragma unroll
         for (int a = 0; a < kAhead; ++a) {
-            lv[a] = q < q1 && k + a < steps;
+            lv[a] = q < q1;
             if (lv[a] && q == next_start) {   // the next unit starts here
+                jq = ahead_j0;
+                tag = ahead_tag;
+                next_start = ahead_next;
+                const int v = min(u, kMaxUnits);   // a lane in its last unit reads past the list
+                ahead_j0 = L.unit[v].y;
+                ahead_next = L.unit[v + 1].x;
+                ahead_tag = L.tag[v];
                 ++u;
-                next_start = L.unit[u + 1].x;
-                jq = L.unit[u].y;
-                tag = L.tag[u];
-                h = L.home[tag >> 8];
             }
-            jj[a] = jq;
+            jj[a] = lv[a] ? jq : s0;
             tg[a] = tag;
-            hh[a] = h;
-            if (lv[a]) {
-                ++jq;
-                ++q;
-            }
+            jq += lv[a] ? 1 : 0;
+            q += lv[a] ? 1 : 0;
         }
 #pragma unroll
-        for (int a = 0; a < kAhead; ++a)
-            if (lv[a]) cc[a] = p.sorted[jj[a]];
+        for (int a = 0; a < kAhead; ++a) cc[a] = p.sorted[jj[a]];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) hh[a] = L.home[tg[a] >> 8];
         // no lane's pairs of these steps need a periodic shift (the common
         // case away from the box faces): plain differences, the same values
         bool plain = false;
@@ -377,44 +383,38 @@ __device__ __forceinline__ void sparse_pairs(const Plan &p, SparseLds &L, EdgeSi
         for (int a = 0; a < kAhead; ++a) {
             const int hl = tg[a] >> 8, code = tg[a] & 63;
             BoxPair bx = bp;
-            if constexpr (!kOneBox) {
-                const int bq = __shfl(b, hl, 64);   // all lanes take part in the shuffle
-                if (lv[a]) bx = BoxPair::of(p.boxes[bq]);
-            }
-            bool link = false;
-            if (lv[a]) {
-                const float4 c = cc[a];
-                const float4 hp = hh[a];
-                if constexpr (kFP64) {
-                    const double tx = ((double)hp.x - (double)c.x) + axis_shift(code & 3, bx.L);
-                    const double ty = ((double)hp.y - (double)c.y) + axis_shift((code >> 2) & 3, bx.L);
-                    const double tz = ((double)hp.z - (double)c.z) + axis_shift((code >> 4) & 3, bx.L);
-                    const double sxy = tx * tx + ty * ty;
-                    const double r2 = sxy + tz * tz;
-                    link = strict ? (r2 < bx.l2) : (r2 <= bx.l2);
+            if constexpr (!kOneBox) bx = BoxPair::of(p.boxes[__shfl(b, hl, 64)]);
+            const float4 c = cc[a], hp = hh[a];
+            bool link;
+            if constexpr (kFP64) {
+                const double tx = ((double)hp.x - (double)c.x) + axis_shift(code & 3, bx.L);
+                const double ty = ((double)hp.y - (double)c.y) + axis_shift((code >> 2) & 3, bx.L);
+                const double tz = ((double)hp.z - (double)c.z) + axis_shift((code >> 4) & 3, bx.L);
+                const double sxy = tx * tx + ty * ty;
+                const double r2 = sxy + tz * tz;
+                link = lv[a] & (strict ? (r2 < bx.l2) : (r2 <= bx.l2));
+            } else {
+                float dx, dy, dz;
+                if (plain) {
+                    dx = hp.x - c.x;
+                    dy = hp.y - c.y;
+                    dz = hp.z - c.z;
                 } else {
-                    float dx, dy, dz;
-                    if (plain) {
-                        dx = hp.x - c.x;
-                        dy = hp.y - c.y;
-                        dz = hp.z - c.z;
-                    } else {
-                        dx = axis_diff(hp.x, c.x, code & 3, bx.L32);
-                        dy = axis_diff(hp.y, c.y, (code >> 2) & 3, bx.L32);
-                        dz = axis_diff(hp.z, c.z, (code >> 4) & 3, bx.L32);
-                    }
-                    const float rr = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                    link = rr < bx.lo32;
-                    // the guard band (rare), decided in double; one branch, the
-                    // compares flat (a NaN lands in the band and fails there)
-                    if (!(rr < bx.lo32) & !(rr > bx.hi32)) {
-                        if (kStats) ++band;
-                        link = link_fp64(hp.x, hp.y, hp.z, c.x, c.y, c.z, bx.L, bx.half, bx.l2, strict);
-                    }
+                    dx = axis_diff(hp.x, c.x, code & 3, bx.L32);
+                    dy = axis_diff(hp.y, c.y, (code >> 2) & 3, bx.L32);
+                    dz = axis_diff(hp.z, c.z, (code >> 4) & 3, bx.L32);
                 }
-                if (kStats) ++tests;
-                if (kStats && link) ++links;
+                const float rr = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                link = lv[a] & (rr < bx.lo32);
+                // the guard band (rare), decided in double; one branch, the
+                // compares flat (a NaN lands in the band and fails there)
+                if (lv[a] & !(rr < bx.lo32) & !(rr > bx.hi32)) {
+                    if (kStats) ++band;
+                    link = link_fp64(hp.x, hp.y, hp.z, c.x, c.y, c.z, bx.L, bx.half, bx.l2, strict);
+                }
             }
+            if (kStats && lv[a]) ++tests;
+            if (kStats && link) ++links;
             // a link inside the tile goes to the tile's bit matrix, the others to the edge list
             const unsigned v = (unsigned)(jj[a] - s0);
             const bool local = in_tile && v < 64u;
