@@ -98,16 +98,28 @@ __global__ void __launch_bounds__(kBlock) k_clear(Plan p)
     clear_run(p, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
 }
 
-// Cell key of input particle i; `ok` tells whether its coordinates are finite
-// and inside [0, L).
-__device__ __forceinline__ int64_t input_key(const Plan &p, int64_t i, float &x, float &y, float &z, bool &ok,
+// The kSortItems input particles of a thread, all read before any is used (a
+// tile is bound by the latency of its loads); the last one past the end.
+__device__ __forceinline__ void load_input(const Plan &p, int64_t first, float (&x)[kSortItems],
+                                           float (&y)[kSortItems], float (&z)[kSortItems])
+{
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k) {
+        const int64_t i = first + k * kBlock;
+        const int64_t at = 3 * (i < p.n ? i : p.n - 1);
+        x[k] = p.pos[at];
+        y[k] = p.pos[at + 1];
+        z[k] = p.pos[at + 2];
+    }
+}
+
+// Cell key of input particle i at (x, y, z); `ok` tells whether its
+// coordinates are finite and inside [0, L).
+__device__ __forceinline__ int64_t input_key(const Plan &p, int64_t i, float x, float y, float z, bool &ok,
                                              BoxHint &hint)
 {
     const int b = p.n_boxes == 1 ? 0 : find_box_hint(p.box_p0, p.n_boxes, i, hint);
     const BoxDev &bd = box_of(p, b);
-    x = p.pos[3 * i + 0];
-    y = p.pos[3 * i + 1];
-    z = p.pos[3 * i + 2];
     ok = in_box(x, bd.L) && in_box(y, bd.L) && in_box(z, bd.L);
     return particle_cell(bd, x, y, z);
 }
@@ -134,13 +146,14 @@ __global__ void __launch_bounds__(kBlock) k_bucket_hist(Plan p)
     for (int b = threadIdx.x; b < kBuckets; b += kBlock) cnt[b] = 0;
     __syncthreads();
     bool bad = false;
+    float x[kSortItems], y[kSortItems], z[kSortItems];
+    load_input(p, tile * kSortTile + threadIdx.x, x, y, z);
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = tile * kSortTile + k * kBlock + threadIdx.x;
         if (i < p.n) {
-            float x, y, z;
             bool ok;
-            const int64_t key = input_key(p, i, x, y, z, ok, hint);
+            const int64_t key = input_key(p, i, x[k], y[k], z[k], ok, hint);
             bad |= !ok;
             atomicAdd(&cnt[(int)(key >> p.bucket_shift)], 1);
         }
@@ -175,21 +188,20 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
     const int64_t base = tile * kSortTile;
     for (int b = threadIdx.x; b < kBuckets; b += kBlock) cnt[b] = 0;
     __syncthreads();
-    float4 v[kSortItems];
+    float x[kSortItems], y[kSortItems], z[kSortItems];
     int bk[kSortItems], rk[kSortItems];
     bool bad = false;
+    load_input(p, base + threadIdx.x, x, y, z);
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         const int64_t i = base + k * kBlock + threadIdx.x;
         bk[k] = -1;
         if (i < p.n) {
-            float x, y, z;
             bool ok;
-            const int64_t key = input_key(p, i, x, y, z, ok, hint);
+            const int64_t key = input_key(p, i, x[k], y[k], z[k], ok, hint);
             bad |= !ok;
             bk[k] = (int)(key >> p.bucket_shift);
             rk[k] = atomicAdd(&cnt[bk[k]], 1);
-            v[k] = make_float4(x, y, z, __int_as_float((int)i));
         }
     }
     if (kPlace == kFew && __ballot(bad) && lane_id() == 0) atomicOr(&p.counters->error, 1u);
@@ -251,7 +263,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_scatter(Plan p)
     for (int k = 0; k < kSortItems; ++k)
         if (bk[k] >= 0) {
             const int at = first[bk[k]] + rk[k];
-            stage[at] = v[k];
+            stage[at] = make_float4(x[k], y[k], z[k], __int_as_float((int)(base + k * kBlock + threadIdx.x)));
             stage_b[at] = (Bucket)bk[k];
         }
     __syncthreads();
@@ -383,8 +395,13 @@ __global__ void __launch_bounds__(kBlock) k_seg_hist(Plan p)
     const int seg0 = b << p.sub_log2;
     for (int s = threadIdx.x; s < subs; s += kBlock) cnt[s] = 0;
     __syncthreads();
-    for (int k = lo + (int)threadIdx.x; k < hi; k += kBlock)
-        atomicAdd(&cnt[(int)(staged_cell(p, p.staging[k], hint) >> p.seg_shift) - seg0], 1);
+    float4 v[kSortItems];
+#pragma unroll
+    for (int q = 0; q < kSortItems; ++q) v[q] = p.staging[min(lo + q * kBlock + (int)threadIdx.x, hi - 1)];
+#pragma unroll
+    for (int q = 0; q < kSortItems; ++q)
+        if (lo + q * kBlock + (int)threadIdx.x < hi)
+            atomicAdd(&cnt[(int)(staged_cell(p, v[q], hint) >> p.seg_shift) - seg0], 1);
     __syncthreads();
     for (int s = threadIdx.x; s < subs; s += kBlock)
         if (cnt[s]) atomicAdd(p.seg_end + seg0 + s, cnt[s]);
