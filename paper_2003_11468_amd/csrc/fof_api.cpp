@@ -52,7 +52,7 @@ struct Layout {
     int64_t scan_tiles = 0;
     int64_t n_tiles = 0;
     int32_t levels = 2, fused_link = 0;
-    int32_t group_parts = 1;
+    int32_t group_parts = 1, group_stride = 1;
     int64_t group_counts = 1;
     int32_t bucket_shift = 0, n_buckets = 1;
     int32_t seg_shift = 0, sub_log2 = 0;
@@ -261,8 +261,9 @@ void fp32_thresholds(BoxDev &b, double lx)
 
 constexpr int kDefaultDenseMin = 32;
 // In cells subdivided to 1.375 l_x eight particles already form groups that
-// the wavefront search joins in registers: 2.1e6 clustered particles take 600,
-// 668, 746 and 914 us with 8, 12, 16 and 32, 1e6 in FP64 506, 561, 651 and 850.
+// the wavefront search joins in registers: a run of 3.3e4 clustered particles
+// takes 90, 94, 103 and 129 us with 4, 8, 12 and 16, 2.1e6 549, 464, 466 and
+// 504, 1e6 in FP64 411, 367, 378 and 405.
 constexpr int kFineDenseMin = 8;
 constexpr int kMaxSubK = 8;              // at most 512 sub-cells per dense cell
 constexpr int kDenseBlocks = 2048;
@@ -407,7 +408,8 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     p.o_p0 = take(sizeof(int64_t) * ((size_t)n_boxes + 1));
     p.o_counters = take(sizeof(Counters));
     p.group_parts = n_boxes < fof::kGroupParts ? fof::kGroupParts / n_boxes : 1;
-    p.group_counts = p.group_parts > 1 ? (int64_t)n_boxes * p.group_parts * fof::kGroupStride : n_boxes;
+    p.group_stride = n_boxes <= fof::kGroupApart ? fof::kGroupStride : 1;
+    p.group_counts = (int64_t)n_boxes * p.group_parts * p.group_stride;
     p.o_groups = take(sizeof(unsigned long long) * (size_t)p.group_counts);
     p.o_cell = take(sizeof(int32_t) * (n + 4));   // starts of the occupied cells (at most n) + sentinels
     p.o_part = take(sizeof(int32_t) * (size_t)p.scan_tiles);
@@ -509,6 +511,7 @@ void carve(const fof_options &o, const Layout &p, const BoxDev &box0, void *ws, 
     d.n_tiles = p.n_tiles;
     d.levels = p.levels;
     d.group_parts = p.group_parts;
+    d.group_stride = p.group_stride;
     d.group_counts = p.group_counts;
     d.fused_link = p.fused_link;
     d.bucket_shift = p.bucket_shift;
@@ -708,9 +711,8 @@ namespace fof {
 int64_t groups_of_box(const void *counts, const Plan &p, int32_t b)
 {
     const unsigned long long *g = static_cast<const unsigned long long *>(counts);
-    if (p.group_parts == 1) return (int64_t)g[b];
     unsigned long long sum = 0;
-    for (int q = 0; q < p.group_parts; ++q) sum += g[((int64_t)b * p.group_parts + q) * kGroupStride];
+    for (int q = 0; q < p.group_parts; ++q) sum += g[((int64_t)b * p.group_parts + q) * p.group_stride];
     return (int64_t)sum;
 }
 

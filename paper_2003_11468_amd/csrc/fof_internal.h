@@ -59,7 +59,8 @@ struct Plan {
     int32_t levels;         // levels of the sort above the cells: 2 buckets and segments, 1 segments
                             // alone (bucket = segment), 0 none (one segment, sorted from the input);
                             // below 2 the results are written straight to input order
-    int32_t group_parts;    // partial group counts per box, kGroupStride entries apart (1: no stride)
+    int32_t group_parts;    // partial group counts per box,
+    int32_t group_stride;   // so many entries apart
     int64_t group_counts;   // entries of n_groups
     int32_t fused_link;     // 1: the per-particle search merges its links itself, beside the pre-merge
     int32_t bucket_shift;   // bucket of a cell = cell >> bucket_shift
@@ -147,7 +148,8 @@ constexpr int kCellOneGroup = 1;
 constexpr int kCellJoined = 2;
 
 constexpr int kGroupParts = 32;    // partial group counts over all boxes, when the boxes are fewer
-constexpr int kGroupStride = 16;   // 128 bytes
+constexpr int kGroupStride = 16;   // 128 bytes between counts of up to kGroupApart boxes
+constexpr int kGroupApart = 128;
 
 // Capacity of the dense work-item list (fof_link.hip).
 int64_t max_dense_items(int64_t n, int dense_min);

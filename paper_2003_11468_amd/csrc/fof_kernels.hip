@@ -63,7 +63,7 @@ __device__ __forceinline__ int32_t *bucket_totals(const Plan &p) { return p.buck
 // their own, summed when they are read.
 __device__ __forceinline__ unsigned long long *group_count(const Plan &p, int b, int block)
 {
-    return p.n_groups + (p.group_parts > 1 ? ((int64_t)b * p.group_parts + block % p.group_parts) * kGroupStride : b);
+    return p.n_groups + ((int64_t)b * p.group_parts + block % p.group_parts) * p.group_stride;
 }
 
 // What a run counts in, zeroed by the threads t of `threads`.
@@ -1005,15 +1005,17 @@ __global__ void __launch_bounds__(kBlock) k_resolve(Plan p)
 
 // Resolve straight into input order (fewer than two sort levels): while the outputs fit in
 // the caches the scattered 4-byte writes cost less than staging slots, their
-// two maps in the sort, a group count and a gather, each a launch. A
-// persistent grid, so that each box's count takes few atomics.
+// two maps in the sort, a group count and a gather, each a launch. Every wave
+// takes a run of consecutive tiles, so it adds to few boxes' counts (with
+// tiles a grid apart 64 boxes of 4.5e5 particles took 31 us instead of 13, with the counts 128 bytes apart).
 __global__ void __launch_bounds__(kBlock) k_resolve_direct(Plan p)
 {
     BoxHint hint;
     int box = -1, roots = 0;   // roots counted in box `box`, the same in every lane
-    const int64_t tiles = (p.n + 63) / 64;
-    const XcdRange xr = xcd_range(tiles, kBlock / 64, threadIdx.x >> 6);
-    for (int64_t tile = xr.first; tile < xr.end; tile += xr.stride) {
+    const int64_t tiles = (p.n + 63) / 64, waves = (int64_t)gridDim.x * (kBlock / 64);
+    const int64_t wave = xcd_tile(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t end = (wave + 1) * tiles / waves;
+    for (int64_t tile = wave * tiles / waves; tile < end; ++tile) {
         const int64_t s64 = tile * 64 + lane_id();
         bool root = false;
         int b = 0;
@@ -1080,7 +1082,7 @@ __global__ void __launch_bounds__(kBlock) k_group_count(Plan p)
             v = (unsigned)p.wave_roots[w];
             if (v) key = find_box(p.box_p0, p.n_boxes, w << 6);
         }
-        wave_add_by_key(group_count(p, 0, blockIdx.x), key < 0 || p.group_parts == 1 ? key : key * p.group_parts * kGroupStride, v);
+        wave_add_by_key(group_count(p, 0, blockIdx.x), key < 0 ? key : key * p.group_parts * p.group_stride, v);
     }
 }
 
