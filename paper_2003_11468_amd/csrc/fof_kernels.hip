@@ -30,10 +30,14 @@
 //   link           (fof_link.hip) cell-pair link search + lock-free union-find
 //   flatten  pointer jumping to the root; group minimum original index
 //            (atomic min) and member count (atomic add) at the root, combined
-//            over runs of equal roots (a wave's last run carries over)
+//            over runs of equal roots (one root stays pending in a wave)
 //   resolve  label and size per sorted slot, stored at its staging slot
 //            (writes stay in bucket windows); per-box group counts
 //   gather   back into input order (reads are runs of each tile's buckets)
+// Small runs, whose time is the launches, take fewer levels (Plan::levels):
+// up to kWideBuckets segments are sorted without buckets, up to kOneSegment
+// particles straight from the input, and their results go straight to input
+// order.
 //
 // The whole translation unit is compiled with -ffp-contract=off: the double
 // predicate below must round every product and sum separately. The FP32

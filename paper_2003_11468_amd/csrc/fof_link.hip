@@ -25,13 +25,13 @@
 // In double, the difference is rounded first and the shift of +-L added after
 // it, which is the very operation sequence of the link predicate.
 //
-// Union-find: each lane keeps the root it last saw for its particle, and each
-// staged candidate carries the root found when it was staged. A linked pair
-// whose two cached roots agree is already in one group and is skipped: both
-// roots were observed as members of the respective groups, and groups only
-// grow. Otherwise the lane hooks the root of lower priority under the other
-// (CAS): by index, the larger under the smaller, or by a fixed pseudo-random
-// priority (randomised linking).
+// Union-find: a merge hooks the root of lower priority under the other by a
+// compare-and-swap: by index, the larger under the smaller, or by a fixed
+// pseudo-random priority (randomised linking). Swaps on a root that others
+// have hooked meanwhile fail and cost a chain of dependent accesses each, so
+// links are gathered where they name the same roots (a tile of the
+// per-particle search, a stage of the wavefront search, a chunk of queued
+// pairs, a dense cell) and every distinct root is hooked once.
 #include <type_traits>
 
 #include "fof_device.h"
