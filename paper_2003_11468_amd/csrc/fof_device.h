@@ -350,21 +350,6 @@ __device__ __forceinline__ bool wave_runs_min_add(int key, int &m, int &c)
     return head && key >= 0;
 }
 
-// Atomic min of `v` into arr[key].y, one atomic per distinct key in the wave.
-__device__ __forceinline__ void wave_min_by_key(int2 *arr, int key, int v)
-{
-    unsigned long long todo = __ballot(key >= 0);
-    while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int k = __shfl(key, leader, 64);
-        const bool mine = key == k;
-        int m = mine ? v : INT_MAX;
-        for (int d = 32; d >= 1; d >>= 1) m = min(m, __shfl_xor(m, d, 64));
-        if (lane_id() == leader) atomicMin(&arr[k].y, m);
-        todo &= ~__ballot(mine);
-    }
-}
-
 __device__ __forceinline__ int64_t particle_cell(const BoxDev &bd, float x, float y, float z)
 {
     const int nc = bd.nc;

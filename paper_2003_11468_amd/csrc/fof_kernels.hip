@@ -868,7 +868,7 @@ __device__ __forceinline__ void add_run(const Plan &p, int key, int m, int c)
 // without any makes its last run the pending one. Where one giant group holds
 // most of the box its root then receives one update per work-group: with
 // single particles of other groups interspersed (2.1e6 lattice sites, 60 %
-// taken) 212 -> 40 us; each of 8192 waves used to end with two atomics there.
+// taken) 212 -> 62 us; each of 8192 waves used to end with two atomics there.
 __global__ void __launch_bounds__(kBlock) k_flatten(Plan p)
 {
     constexpr int kFlatIlp = 4;   // stretches whose chases advance together

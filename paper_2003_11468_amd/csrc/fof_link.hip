@@ -1395,10 +1395,10 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
 // it; cells found to be one group are marked, and the pair search passes over
 // marked neighbours of the home particles' own group. Both kernels are bound
 // by the latency of their dependent loads, so what counts is how few an item
-// needs: on 256 boxes of 1e3 to 1e6 particles (232k items) the pair search
-// went from 1.58 to 1.10 ms and the pre-merge from 0.44 to 0.39 ms; on 1e5
-// particles, where a few halo cores were the tail, the search from 157 to 54
-// us. A larger cell is split into k^3 sub-cells small enough that any two
+// needs: on 256 boxes of 1e3 to 1e6 particles (232k items) the pre-merge went
+// from 0.44 to 0.33 ms, and the pair search from 1.58 to 1.10 ms by what it
+// spares there; on 1e5 particles, where a few halo cores were the tail, the
+// search from 157 to 54 us. A larger cell is split into k^3 sub-cells small enough that any two
 // particles of one sub-cell are linked. When the sub-cells are smaller still (sub_adj:
 // any two particles of two sub-cells that touch, across a face, an edge or a
 // corner, are linked), a union-find over the occupied sub-cells in LDS joins
