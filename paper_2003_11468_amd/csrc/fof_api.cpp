@@ -148,13 +148,17 @@ struct fof_ctx {
     bool stage_pending[2] = {false, false};
     int stage_next = 0;
 
-    // Host memory for what is read back: pinned from the second read on, and
-    // grown when a larger one comes. A copy into pageable memory makes the
-    // runtime wait and copy again, 10 us, 23 with seven launches before it; a
-    // context that reads once saves the allocation instead, which costs more.
+    // Host memory for what is read back: pinned from the third read on, or from
+    // the first that waits for a run long enough to hide the allocation
+    // (kHidePinned particles, 0.4 ms), and grown when a larger one comes. A copy
+    // into pageable memory makes the runtime wait and copy again, 10 us, 23 with
+    // seven launches before it; a context that reads once or twice saves the
+    // allocation instead, which costs more (a catalogue of 4e6 particles after
+    // one run: 82 us with the allocation, 68 into pageable memory).
     char *read_buf = nullptr;
     size_t read_bytes = 0;
-    std::vector<char> first_read;
+    std::vector<char> pageable;
+    int reads = 0;
 
     int state = 0;             // 0 idle, 1 cells built, 2 linked
     bool cells_valid = false;  // the last build's cells and sorted positions are in the workspace
@@ -663,22 +667,31 @@ fof_status enqueue_build(fof_ctx *c, hipStream_t s)
 }
 
 // Copies `bytes` bytes at d_src to the context's read buffer, in stream order,
-// and waits for them.
-fof_status read_device(fof_ctx *c, const void *d_src, size_t bytes, const char **out)
+// and waits for them. `busy`: the stream has a whole run before the copy.
+fof_status read_device(fof_ctx *c, const void *d_src, size_t bytes, bool busy, const char **out)
 {
+    constexpr int64_t kHidePinned = 1 << 20;
+    constexpr int kEarlyReads = 2;
     char *to = c->read_buf;
-    if (c->first_read.empty()) {
-        c->first_read.resize(bytes);
-        to = c->first_read.data();
-    } else if (c->read_bytes < bytes) {
-        if (c->read_buf) (void)hipHostFree(c->read_buf);
-        c->read_buf = nullptr;
-        c->read_bytes = 0;
+    if (c->read_bytes < bytes && (c->reads >= kEarlyReads || (busy && c->plan.n >= kHidePinned))) {
+        // a capture that another stream has open must not see the allocation
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         void *buf = nullptr;
-        if (hipHostMalloc(&buf, bytes, hipHostMallocDefault) != hipSuccess) return FOF_ERR_DEVICE;
-        c->read_buf = to = static_cast<char *>(buf);
-        c->read_bytes = bytes;
+        if (hipHostMalloc(&buf, bytes, hipHostMallocDefault) == hipSuccess) {
+            if (c->read_buf) (void)hipHostFree(c->read_buf);
+            c->read_buf = to = static_cast<char *>(buf);
+            c->read_bytes = bytes;
+        } else {
+            (void)hipGetLastError();   // the copy goes to pageable memory
+        }
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
+    if (c->read_bytes < bytes) {
+        c->pageable.resize(bytes);
+        to = c->pageable.data();
+    }
+    if (c->reads < kEarlyReads) ++c->reads;
     if (hipMemcpyAsync(to, d_src, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
         return FOF_ERR_DEVICE;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return FOF_ERR_DEVICE;
@@ -692,7 +705,7 @@ fof_status read_back(fof_ctx *c, int64_t *h_n_groups, Counters *h_counters)
     // the counters and, behind them in the workspace, the group counts: one copy
     const size_t bytes = (p.o_groups - p.o_counters) + sizeof(unsigned long long) * (size_t)p.group_counts;
     const char *buf = nullptr;
-    const fof_status st = read_device(c, c->dev.counters, bytes, &buf);
+    const fof_status st = read_device(c, c->dev.counters, bytes, true, &buf);
     if (st != FOF_OK) return st;
     Counters cnt;
     std::memcpy(&cnt, buf, sizeof(cnt));
@@ -885,7 +898,7 @@ fof_status fof_catalogue(fof_ctx *ctx, const int32_t *d_group_index, const int32
                                                   capacity, ctx->stream));
     if (st != FOF_OK) return st;
     const char *total = nullptr;
-    st = read_device(ctx, p.bucket_hist + p.n_tiles, sizeof(int), &total);
+    st = read_device(ctx, p.bucket_hist + p.n_tiles, sizeof(int), false, &total);
     if (st != FOF_OK) return st;
     *h_count = *reinterpret_cast<const int *>(total);
     return FOF_OK;
