@@ -718,8 +718,10 @@ static_assert(kUnionSlots >= 4 * kUnionChunk, "at most 2 roots per pair, and roo
 // is hooked under its label by one compare-and-swap; one that finds the root
 // moved goes on as an ordinary union, and so do pairs whose labels had not
 // met after kUnionRounds rounds. 2.1e6 clustered particles (0.49M pairs) 91 ->
-// 48 us, 256 boxes (15.8M) 0.80 -> 0.37 ms, 2.1e6 lattice sites 345 -> 194 us
-// (2 pairs per lane: 60, 0.36, 320; 8: 58, 0.42, 168).
+// 48 us, 256 boxes (15.8M) 0.80 -> 0.37 ms, 2.1e6 lattice sites, where all
+// swaps meet on a few roots, 345 -> 194 .. 266 us with where the forest lies in
+// memory (beside 194: 2 pairs per lane 60 us, 0.36 ms, 320 us; 8: 58, 0.42,
+// 168).
 // Slice s holds the pairs found on XCD s % 8 (the search's work-group b
 // appends to slice b % 256, and work-groups go to XCDs round-robin), whose
 // home particles are that XCD's contiguous range of cells; its kUnionParts
