@@ -194,15 +194,18 @@ bool options_valid(const fof_options &o)
     return true;
 }
 
+double root_of(int64_t n_box) { return std::cbrt((double)(n_box > 1 ? n_box : 1)); }
+
 // Cells per axis for one box: as many as the option asks for (cells of about
 // one particle by default), never narrower than l_x (1 + 2^-20), at least 3.
-fof_status cells_per_axis(const fof_options &o, int64_t n_box, double L, double lx, int64_t *nc_out)
+// `root`: the cube root of the box's particles.
+fof_status cells_per_axis(const fof_options &o, double root, double L, double lx, int64_t *nc_out)
 {
     const double fit = std::floor(L / (lx * (1.0 + 1.0 / 1048576.0)));
     if (!(fit >= 3.0)) return FOF_ERR_INVALID_ARG;
     double want;
     if (o.cell_factor > 0.0) want = std::floor(L / (o.cell_factor * lx));
-    else want = std::floor(std::cbrt((double)(n_box > 1 ? n_box : 1)) + 1e-9);
+    else want = std::floor(root + 1e-9);
     double nc = want < fit ? want : fit;
     if (nc < 3.0) nc = 3.0;
     if (nc > kMaxCellsPerAxis) return FOF_ERR_UNSUPPORTED;
@@ -215,19 +218,20 @@ fof_status cells_per_axis(const fof_options &o, int64_t n_box, double L, double 
 // and a cell inside a halo then holds thousands of particles, all tested
 // against all. Cells are indexed by rank, so empty ones cost only 2 bits: with
 // automatic cells the search subdivides them to 1.375 l_x, the side the sweep
-// over 1 .. 4 l_x found best for clustered boxes, as far as kRefineCells cells
-// per particle (16 bytes of occupancy words each, a sixth of the workspace)
-// and the 2048 cells per axis allow. A cell factor given by the caller is
-// taken as it is.
+// over 1 .. 4 l_x found best for clustered boxes, as far as kRefineAxis^3 = 64
+// cells per particle (16 bytes of occupancy words each, a sixth of the
+// workspace) and the 2048 cells per axis allow. A cell factor given by the
+// caller is taken as it is.
 constexpr double kRefineSide = 1.375;
-constexpr double kRefineCells = 64.0;
+constexpr double kRefineAxis = 4.0;
 constexpr double kOneSegmentCells = 40.0;   // per axis: 64000 cells, of the 2^16 a segment holds
 
-int64_t search_cells_per_axis(const fof_options &o, int64_t n_box, double L, double lx, int64_t nc, bool only_box)
+int64_t search_cells_per_axis(const fof_options &o, int64_t n_box, double root, double L, double lx, int64_t nc,
+                              bool only_box)
 {
     if (o.cell_factor > 0.0 || n_box < 1) return nc;
     double want = std::floor(L / (kRefineSide * lx));
-    const double most = std::floor(std::cbrt(kRefineCells * (double)n_box));
+    const double most = std::floor(kRefineAxis * root);
     if (want > most) want = most;
     if (want > kMaxCellsPerAxis) want = kMaxCellsPerAxis;
     // a run small enough for one segment keeps its cells within one
@@ -303,28 +307,38 @@ int dense_min_of(const fof_options &o, bool fine)
     return o.dense_min > 0 ? o.dense_min : (fine ? kFineDenseMin : kDefaultDenseMin);
 }
 
-// Validates one box (nb particles, side L, linking length l) and fills its
-// descriptor, cells starting at global cell `cell_base`; `refine`: on the
-// search's own grid (search_cells_per_axis).
-fof_status box_geometry(const fof_options &o, int64_t nb, double L, double l, int64_t cell_base, bool refine,
-                        bool only_box, BoxDev *out)
+// Cells per axis of one box: as the options ask for them, and as the search
+// subdivides them.
+struct AxisCells {
+    int32_t asked, search;
+};
+
+// Validates one box (nb particles, side L, linking length l) and counts its cells.
+fof_status box_cells(const fof_options &o, int64_t nb, double L, double l, bool only_box, AxisCells *out)
 {
     if (!(L > 0.0) || !std::isfinite(L) || !(l > 0.0) || !std::isfinite(l)) return FOF_ERR_INVALID_ARG;
     int64_t nc = 0;
-    fof_status st = cells_per_axis(o, nb, L, l, &nc);
+    const double root = o.cell_factor > 0.0 ? 0.0 : root_of(nb);   // used by automatic cells alone
+    fof_status st = cells_per_axis(o, root, L, l, &nc);
     if (st != FOF_OK) return st;
-    if (refine) nc = search_cells_per_axis(o, nb, L, l, nc, only_box);
+    out->asked = (int32_t)nc;
+    out->search = (int32_t)search_cells_per_axis(o, nb, root, L, l, nc, only_box);
+    return FOF_OK;
+}
+
+// Descriptor of a box of nc cells per axis that start at global cell `cell_base`.
+void box_geometry(double L, double l, int32_t nc, int64_t cell_base, BoxDev *out)
+{
     BoxDev &b = *out;
     std::memset(&b, 0, sizeof(b));
     b.cell_base = cell_base;
-    b.nc = (int32_t)nc;
+    b.nc = nc;
     b.L = L;
     b.half = 0.5 * L;
     b.inv_h = (double)nc / L;
     b.l2 = l * l;
     fp32_thresholds(b, l);
     sub_cells(L, nc, l, &b.sub_k, &b.sub_adj);
-    return FOF_OK;
 }
 
 // Sizes up to which a run is laid out for few launches; each line lies where
@@ -446,51 +460,71 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     return FOF_OK;
 }
 
-// `coarse`: the plan with the cells the options ask for, to be subdivided for
-// the search; null for that plan itself.
-fof_status make_plan_on(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx,
-                        int32_t n_boxes, const HostPlan *coarse, HostPlan *out)
+int64_t cube(int64_t nc) { return nc * nc * nc; }
+
+// Validates the boxes and lays out their run in a workspace of `bytes` bytes.
+// Every request is judged by the cells the options ask for; their subdivision
+// is taken (Layout::fine) where its cells are within the limits and the
+// workspace holds it. `need`: the larger of the two sizes, so a workspace of
+// that size serves either. One pass over the boxes counts both kinds of cells
+// and keeps nothing else, since a batch of tiny boxes waits for its planning:
+// 2e4 boxes of 20 particles take 1.1 ms a run, 2.6 with two whole plans made
+// here and one more at each build. `axis`: the cells of each box; may be null.
+fof_status size_run(const fof_options &o, const int64_t *offsets, const double *box, const double *lx,
+                    int32_t n_boxes, size_t bytes, AxisCells *axis, Layout *out, size_t *need)
 {
     if (!offsets || !box || !lx || n_boxes < 1) return FOF_ERR_INVALID_ARG;
     if (offsets[0] != 0) return FOF_ERR_INVALID_ARG;
-    HostPlan p;
-    p.boxes.resize((size_t)n_boxes);
-    p.p0.assign(offsets, offsets + n_boxes + 1);
-    int64_t cells = 0;
+    int64_t cells = 0, fine_cells = 0;
+    bool fine_fits = o.cell_factor == 0.0;
     for (int32_t k = 0; k < n_boxes; ++k) {
         const int64_t nb = offsets[k + 1] - offsets[k];
         if (nb < 0 || offsets[k + 1] > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
-        BoxDev &b = p.boxes[(size_t)k];
-        fof_status st = box_geometry(c->opt, nb, box[k], lx[k], cells, coarse != nullptr, n_boxes == 1, &b);
+        AxisCells a;
+        const fof_status st = box_cells(o, nb, box[k], lx[k], n_boxes == 1, &a);
         if (st != FOF_OK) return st;
-        b.p0 = offsets[k];
-        b.p1 = offsets[k + 1];
-        p.lx_cells.push_back(lx[k]);
-        if (c->opt.predicate == FOF_PRED_FP32_FILTER && b.use_fp64) ++p.fp64_boxes;
-        cells += (int64_t)b.nc * b.nc * b.nc;
+        if (axis) axis[k] = a;
+        cells += cube(a.asked);
         if (cells > kMaxCells) return FOF_ERR_UNSUPPORTED;
+        if (fine_fits) fine_cells += cube(a.search);
+        if (fine_cells > kMaxCells) fine_fits = false;
     }
-    fof_status st = make_layout(c->opt, offsets[n_boxes], cells, n_boxes, coarse && cells > coarse->n_cells, &p);
+    const fof_status st = make_layout(o, offsets[n_boxes], cells, n_boxes, false, out);
     if (st != FOF_OK) return st;
-    *out = std::move(p);
+    *need = out->total;
+    Layout fine;
+    if (!fine_fits || fine_cells <= cells ||
+        make_layout(o, offsets[n_boxes], fine_cells, n_boxes, true, &fine) != FOF_OK)
+        return FOF_OK;
+    if (fine.total > *need) *need = fine.total;
+    if (fine.total <= bytes) *out = fine;
     return FOF_OK;
 }
 
-// The plan of a run in a workspace of `bytes` bytes. Every request is judged
-// by the cells the options ask for; their subdivision is taken where its
-// cells are within the limits and the workspace holds it. `need`: the larger
-// of the two sizes, so a workspace of that size serves either.
+// The plan of a run in the context's workspace.
 fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx, int32_t n_boxes,
-                     size_t bytes, HostPlan *out, size_t *need)
+                     HostPlan *out)
 {
-    fof_status st = make_plan_on(c, offsets, box, lx, n_boxes, nullptr, out);
+    if (!offsets || n_boxes < 1) return FOF_ERR_INVALID_ARG;
+    HostPlan p;
+    size_t need = 0;
+    std::vector<AxisCells> axis((size_t)n_boxes);
+    const fof_status st = size_run(c->opt, offsets, box, lx, n_boxes, c->ws_bytes, axis.data(), &p, &need);
     if (st != FOF_OK) return st;
-    *need = out->total;
-    if (c->opt.cell_factor > 0.0) return FOF_OK;
-    HostPlan fine;
-    if (make_plan_on(c, offsets, box, lx, n_boxes, out, &fine) != FOF_OK) return FOF_OK;
-    if (fine.total > *need) *need = fine.total;
-    if (fine.total <= bytes) *out = std::move(fine);
+    p.boxes.resize((size_t)n_boxes);
+    p.p0.assign(offsets, offsets + n_boxes + 1);
+    p.lx_cells.assign(lx, lx + n_boxes);
+    int64_t cells = 0;
+    for (int32_t k = 0; k < n_boxes; ++k) {
+        BoxDev &b = p.boxes[(size_t)k];
+        const AxisCells &a = axis[(size_t)k];
+        box_geometry(box[k], lx[k], p.fine ? a.search : a.asked, cells, &b);
+        b.p0 = offsets[k];
+        b.p1 = offsets[k + 1];
+        if (c->opt.predicate == FOF_PRED_FP32_FILTER && b.use_fp64) ++p.fp64_boxes;
+        cells += cube(b.nc);
+    }
+    *out = std::move(p);
     return FOF_OK;
 }
 
@@ -651,8 +685,7 @@ fof_status do_build(fof_ctx *c, const float *d_pos, const int64_t *off, const do
         if (!c->timer || !c->timer->init()) return FOF_ERR_DEVICE;
     }
     HostPlan np;
-    size_t need = 0;
-    fof_status st = make_plan(c, off, box, lx, n_boxes, c->ws_bytes, &np, &need);
+    fof_status st = make_plan(c, off, box, lx, n_boxes, &np);
     if (st != FOF_OK) return st;
     if (!d_pos && np.n > 0) return FOF_ERR_INVALID_ARG;
     st = install_plan(c, std::move(np));
@@ -734,24 +767,14 @@ fof_status plan_one_box(const fof_options &o, int64_t n, double box, double lx, 
 {
     *need = 0;
     if (!options_valid(o)) return FOF_ERR_INVALID_ARG;
-    if (n < 0 || n > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
-    BoxDev b;
-    fof_status st = box_geometry(o, n, box, lx, 0, false, true, &b);
-    if (st != FOF_OK) return st;
+    const int64_t offsets[2] = {0, n};
+    AxisCells axis;
     Layout lay;
-    st = make_layout(o, n, (int64_t)b.nc * b.nc * b.nc, 1, false, &lay);
+    size_t most = 0;
+    const fof_status st = size_run(o, offsets, &box, &lx, 1, bytes, &axis, &lay, &most);
     if (st != FOF_OK) return st;
-    if (o.cell_factor == 0.0) {   // the subdivided cells, where they fit
-        BoxDev fine_box;
-        Layout fine;
-        if (box_geometry(o, n, box, lx, 0, true, true, &fine_box) == FOF_OK &&
-            fine_box.nc > b.nc &&
-            make_layout(o, n, (int64_t)fine_box.nc * fine_box.nc * fine_box.nc, 1, true, &fine) == FOF_OK &&
-            fine.total <= bytes) {
-            b = fine_box;
-            lay = fine;
-        }
-    }
+    BoxDev b;
+    box_geometry(box, lx, lay.fine ? axis.search : axis.asked, 0, &b);
     b.p0 = 0;
     b.p1 = n;
     *need = lay.total;
@@ -798,9 +821,9 @@ fof_status fof_workspace_bytes(fof_ctx *ctx, const int64_t *h_box_offsets, const
                                int32_t n_boxes, size_t *bytes)
 {
     if (!ctx || !bytes) return FOF_ERR_INVALID_ARG;
-    HostPlan p;
+    Layout lay;
     size_t need = 0;
-    fof_status st = make_plan(ctx, h_box_offsets, h_box, h_lx, n_boxes, 0, &p, &need);
+    fof_status st = size_run(ctx->opt, h_box_offsets, h_box, h_lx, n_boxes, 0, nullptr, &lay, &need);
     if (st != FOF_OK) return st;
     *bytes = need;
     return FOF_OK;
@@ -1025,7 +1048,7 @@ fof_status fof_describe_box(const fof_options *opt, int64_t n_particles, double 
     if (n_particles < 0 || n_particles > (int64_t)INT32_MAX) return FOF_ERR_INVALID_ARG;
     if (!(box > 0.0) || !std::isfinite(box) || !(lx > 0.0) || !std::isfinite(lx)) return FOF_ERR_INVALID_ARG;
     int64_t nc = 0;
-    fof_status st = cells_per_axis(o, n_particles, box, lx, &nc);
+    fof_status st = cells_per_axis(o, root_of(n_particles), box, lx, &nc);
     if (st != FOF_OK) return st;
     BoxDev b;
     std::memset(&b, 0, sizeof(b));
