@@ -355,12 +355,13 @@ constexpr int64_t kOneLevelMax = 900000;
 constexpr int64_t kFusedLinkMax = 1 << 17;
 
 // Sort levels and the workspace carve-up for n particles in `cells` cells
-// over n_boxes boxes.
-fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int32_t n_boxes, bool fine,
+// over n_boxes boxes, where the options ask for `asked` cells: more cells are
+// their subdivision (Layout::fine).
+fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int64_t asked, int32_t n_boxes,
                        Layout *out)
 {
     Layout p;
-    p.fine = fine;
+    const bool fine = p.fine = cells > asked;
     p.n_boxes = n_boxes;
     p.n = n_total;
     p.n_cells = cells;
@@ -373,7 +374,13 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     // By default a segment holds about kSegTarget particles on average (its
     // particles are then placed through LDS), within 2^6 .. 2^16 cells.
     if (o.sort_segment_log2) {
+        // A size given in the cells asked for keeps about its particles where
+        // these are subdivided: taken in the subdivided cells, 2^10 of them
+        // hold 21 particles instead of 1024 at b = 0.2 (1e6 uniform particles
+        // 344 us a run instead of 189).
         p.seg_shift = o.sort_segment_log2;
+        while (p.seg_shift < fof::kSegLog2Max && (asked << (p.seg_shift + 1 - o.sort_segment_log2)) <= cells)
+            ++p.seg_shift;
     } else {
         const double want = (double)fof::kSegTarget * (double)(cells > 0 ? cells : 1) /
                             (double)(n_total > 0 ? n_total : 1);
@@ -489,12 +496,12 @@ fof_status size_run(const fof_options &o, const int64_t *offsets, const double *
         if (fine_fits) fine_cells += cube(a.search);
         if (fine_cells > kMaxCells) fine_fits = false;
     }
-    const fof_status st = make_layout(o, offsets[n_boxes], cells, n_boxes, false, out);
+    const fof_status st = make_layout(o, offsets[n_boxes], cells, cells, n_boxes, out);
     if (st != FOF_OK) return st;
     *need = out->total;
     Layout fine;
     if (!fine_fits || fine_cells <= cells ||
-        make_layout(o, offsets[n_boxes], fine_cells, n_boxes, true, &fine) != FOF_OK)
+        make_layout(o, offsets[n_boxes], fine_cells, cells, n_boxes, &fine) != FOF_OK)
         return FOF_OK;
     if (fine.total > *need) *need = fine.total;
     if (fine.total <= bytes) *out = fine;
