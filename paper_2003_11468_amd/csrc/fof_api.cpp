@@ -354,6 +354,13 @@ void box_geometry(double L, double l, int32_t nc, int64_t cell_base, BoxDev *out
 constexpr int64_t kOneLevelMax = 900000;
 constexpr int64_t kFusedLinkMax = 1 << 17;
 
+// The group counts kept apart (16 KB) and the occupancy words of a single
+// segment (8 KB more than of segments that end with the cells) come out of the
+// edge list, a quarter of a per cent of its least size, so that a workspace of
+// given cells stays as small as without them.
+constexpr int64_t kEdgesSpared = 4096;
+static_assert(kEdgesSpared % fof::kEdgeSlices == 0, "whole slices");
+
 // Sort levels and the workspace carve-up for n particles in `cells` cells
 // over n_boxes boxes, where the options ask for `asked` cells: more cells are
 // their subdivision (Layout::fine).
@@ -389,15 +396,20 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     }
     if (p.seg_shift < p.bucket_shift - fof::kMaxSubLog2) p.seg_shift = p.bucket_shift - fof::kMaxSubLog2;
     if (p.seg_shift > fof::kSegLog2Max) return FOF_ERR_UNSUPPORTED;   // more cells than the levels hold
+    p.n_tiles = fof::sort_tiles_for(n_total);
     // Fewer levels for fewer segments, so that small runs, whose time is the
     // launches, need fewer: up to kWideBuckets segments are sorted without
-    // buckets, and up to kOneSegment particles in at most one segment's cells
-    // straight from the input. Per-kernel timers time the general path.
+    // buckets, where the segment-order buffer, which such a run does not need
+    // for its particles, holds its counts; and up to kOneSegment particles in
+    // at most one segment's cells straight from the input. Per-kernel timers
+    // time the general path.
     if (!o.collect_timings && n_total > 0) {
+        const int64_t segments = (last >> p.seg_shift) + 1;
         if (n_total <= fof::kOneSegment && cells <= (int64_t)1 << fof::kSegLog2Max && !o.sort_segment_log2) {
             p.levels = 0;
             while ((last >> p.seg_shift) > 0) ++p.seg_shift;
-        } else if ((last >> p.seg_shift) < fof::kWideBuckets && n_total <= kOneLevelMax) {
+        } else if (segments <= fof::kWideBuckets && n_total <= kOneLevelMax &&
+                   segments * (p.n_tiles + 1) <= 4 * n_total) {
             p.levels = 1;
         }
         if (p.levels < 2) p.bucket_shift = p.seg_shift;
@@ -407,10 +419,9 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     p.sub_log2 = p.bucket_shift - p.seg_shift;
     p.n_buckets = (int32_t)((last >> p.bucket_shift) + 1);
     p.n_segments = (last >> p.seg_shift) + 1;
-    p.n_tiles = fof::sort_tiles_for(n_total);
     {
         const int64_t a = fof::scan_scratch_for(p.n_segments);
-        const int64_t b = fof::scan_scratch_for((int64_t)p.n_buckets * p.n_tiles);
+        const int64_t b = p.levels == 2 ? fof::scan_scratch_for((int64_t)p.n_buckets * p.n_tiles) : 1;
         const int64_t t = fof::scan_scratch_for(p.n_tiles + 1);   // the group catalogue
         p.scan_tiles = a > b ? a : b;
         if (t > p.scan_tiles) p.scan_tiles = t;
@@ -449,10 +460,10 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     // linked pairs of sparse cells, merged after the search; a pair that finds
     // the list full is merged on the spot instead
     p.max_edges = n_total > (1 << 20) ? n_total : (1 << 20);
-    p.max_edges = (p.max_edges + fof::kEdgeSlices - 1) / fof::kEdgeSlices * fof::kEdgeSlices;
+    p.max_edges = (p.max_edges + fof::kEdgeSlices - 1) / fof::kEdgeSlices * fof::kEdgeSlices - kEdgesSpared;
     p.o_edges = take(sizeof(int32_t) * 2 * (size_t)p.max_edges);
     p.o_edge_fill = take(sizeof(uint32_t) * fof::kEdgeSlices);
-    p.o_hist = take(sizeof(int32_t) * ((size_t)p.n_buckets * ((size_t)p.n_tiles + 1) + 1));
+    if (p.levels != 1) p.o_hist = take(sizeof(int32_t) * ((size_t)p.n_buckets * (size_t)p.n_tiles + 1));
     p.o_staging = take(sizeof(float) * 4 * n);
     p.o_stpos = take(sizeof(int32_t) * n);
     p.o_wave_roots = take(sizeof(int32_t) * ((n + 63) / 64));
@@ -460,6 +471,7 @@ fof_status make_layout(const fof_options &o, int64_t n_total, int64_t cells, int
     p.o_occ = take(sizeof(uint2) * (((size_t)p.n_segments << (p.seg_shift - 5)) + 2));
     p.o_seg = take(sizeof(int32_t) * (size_t)p.n_segments);
     p.o_staging2 = take(sizeof(float) * 4 * n);
+    if (p.levels == 1) p.o_hist = p.o_staging2;
     p.o_stage2_k = take(sizeof(int32_t) * n);
     p.o_bnd = o.domains > 1 ? take(sizeof(int32_t) * 2 * (size_t)p.max_edges) : 0;
     p.total = at;

@@ -91,11 +91,14 @@ struct Plan {
                             // entries n .. n + 3 hold n
     int32_t *seg_end;       // [n_segments] counts, exclusive prefix, then (after the segment pass) end slots
     int32_t *scan_part;     // [scan_tiles] tile sums of every scan level
-    int32_t *bucket_hist;   // [n_buckets * n_tiles + 1] counts, then output offsets (bucket-major);
-                            // the group catalogue reuses it for its tile counts
+    int32_t *bucket_hist;   // levels 2: [n_buckets * n_tiles + 1] counts, then output offsets
+                            // (bucket-major); levels 1: [n_buckets * (n_tiles + 1)] counts or offsets
+                            // (tile-major) and, behind them, the buckets' totals, in the memory of
+                            // staging2; the group catalogue reuses it for its n_tiles + 1 counts
     float4 *staging;        // [n] bucket order: x, y, z, original index (bits); after resolve: {label, size}
     int32_t *stpos;         // [n] staging slot of input particle i
-    float4 *staging2;       // [n] segment order (cells of a segment together, unordered inside)
+    float4 *staging2;       // [n] levels 2: segment order (cells of a segment together, unordered inside);
+                            // then the global merge of domain mode
     int32_t *stage2_k;      // [n] staging slot of each segment-order slot
     uint2 *occ;             // [n_segments << (seg_shift - 5) + 2] per 32 cells: .x bit k: cell 32w + k
                             // holds a particle; .y the cstart index of the first occupied cell at or

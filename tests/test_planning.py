@@ -1,9 +1,14 @@
-"""How runs are planned on the host (no device): what planning a batch costs."""
+"""How runs are planned: what planning a batch costs on the host, and which
+workspaces hold which runs."""
 from __future__ import annotations
 
 import time
 
 import numpy as np
+import pytest
+
+import oracle
+import synth
 
 import paper_2003_11468_amd as fof
 
@@ -48,3 +53,95 @@ def test_a_given_segment_size_keeps_its_particles_in_subdivided_cells():
         # twice the segments that the cells asked for have, the last segment's
         # occupancy words (8 bytes per 32 cells of at most 2^16) and padding
         assert need[k] - need[16] <= 4 * 2 * (cells >> k) + (1 << 14) + 4096, (k, need)
+
+
+# Boxes of `per` particles each at b = 0.2, options, and the bytes of a
+# workspace that holds their run on the cells that the options ask for: the
+# memory of the pipeline before small runs took fewer launches, which may not
+# grow, since callers with a fixed buffer would be refused.
+HELD = [
+    (1000, 1, {}, 8475392), (4000, 1, {}, 8718592), (30_000, 1, {}, 10831104), (900_000, 1, {}, 81842432),
+    (1_500_000, 1, {}, 134320128), (1500, 40, {}, 13273600), (700, 128, {}, 15697152), (700, 199, {}, 19770880),
+    (4000, 1, dict(segment_log2=8), 8718336), (900_000, 1, dict(domains=3), 90232576),
+]
+
+
+def needed(offsets, lx, **kw):
+    ctx = fof.fof_create(fof.make_options(**kw))
+    try:
+        return fof.fof_workspace_bytes(ctx, offsets, 1.0, lx)
+    finally:
+        fof.fof_destroy(ctx)
+
+
+@pytest.mark.parametrize("per,boxes,kw,held", HELD)
+def test_a_run_needs_no_more_memory_than_it_did(per, boxes, kw, held):
+    lx = 0.2 / per ** (1.0 / 3.0)
+    nc = fof.fof_describe_box(per, 1.0, lx)["cells_per_axis"]
+    # the automatic cells, given: no subdivision takes its share
+    assert needed(np.arange(boxes + 1) * per, lx, cell_factor=1.0 / (lx * (nc + 0.5)), **kw) <= held
+
+
+@pytest.mark.parametrize("n", [4080, 131_072, 900_000])
+@pytest.mark.parametrize("factor", [0.0, 1.0, 1.375])
+def test_one_particle_more_never_needs_less(n, factor):
+    """A workspace sized for the larger run holds the smaller one: also where
+    the smaller run is laid out for fewer launches."""
+    sizes = [needed([0, m], 0.2 / m ** (1.0 / 3.0), cell_factor=factor) for m in (n, n + 1)]
+    assert sizes[0] <= sizes[1]
+
+
+def test_the_no_allocation_scratch_holds_what_it_held():
+    n = 1_498_880   # the most particles at b = 0.2 that the scratch held
+    lx = 0.2 / n ** (1.0 / 3.0)
+    nc = fof.fof_describe_box(n, 1.0, lx)["cells_per_axis"]
+    assert needed([0, n], lx, cell_factor=1.0 / (lx * (nc + 0.5))) <= fof.NOALLOC_SCRATCH_BYTES
+    # subdivided cells may need more: the entry then takes the others
+    assert needed([0, n], lx) > fof.NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("per,boxes,kw,held", [h for h in HELD if h[0] != 1_500_000])
+def test_runs_in_the_least_workspace(per, boxes, kw, held):
+    """Labels, a relink and catalogues before and after it (their counts lie
+    where the sort's were), on memory that holds nothing useful before."""
+    import torch
+
+    n = per * boxes
+    off = np.arange(boxes + 1, dtype=np.int64) * per
+    lx = 0.2 / per ** (1.0 / 3.0)
+    pos_np = np.concatenate([synth.clustered(per, 11, k, 0.6) for k in range(boxes)])
+    pos = torch.from_numpy(pos_np).cuda()
+    f = fof.FoF(**kw)
+    try:
+        f.ws = torch.full((held,), 255, dtype=torch.uint8, device="cuda")
+        fof.fof_set_workspace(f.ctx, f.ws)
+        label, size = f.outputs(n)
+        fof.fof_build_cells(f.ctx, pos, off, 1.0, lx)
+        for scale in (1.0, 0.7):
+            if scale < 1.0:
+                fof.fof_relink(f.ctx, scale * lx, boxes)
+            fof.fof_link(f.ctx)
+            ng = fof.fof_finalize(f.ctx, label, size, boxes)
+            ref = oracle.fof_boxes(pos_np, off, np.ones(boxes), np.full(boxes, scale * lx))
+            assert np.array_equal(label.cpu().numpy(), ref[0]) and np.array_equal(size.cpu().numpy(), ref[1])
+            assert np.array_equal(ng, ref[2])
+            first, gsize, box = f.catalogue(label, size, 2)
+            at = np.flatnonzero(ref[1] >= 2)
+            assert np.array_equal(first.cpu().numpy(), ref[0][at]) and np.array_equal(gsize.cpu().numpy(), ref[1][at])
+            assert np.array_equal(box.cpu().numpy(), at // per)
+    finally:
+        f.close()
+
+
+@pytest.mark.gpu
+def test_no_allocation_run_of_the_largest_size_held():
+    import torch
+
+    n = 1_498_880
+    lx = 0.2 / n ** (1.0 / 3.0)
+    pos = torch.from_numpy(synth.clustered(n, 12, 0, 0.6)).cuda()
+    label, size = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    ng = fof.fof_label_noalloc(pos, 1.0, lx, label, size, stream=torch.cuda.current_stream().cuda_stream)
+    ref = fof.label(pos, lx)
+    assert torch.equal(label, ref[0]) and torch.equal(size, ref[1]) and ng == ref[2]
