@@ -520,29 +520,48 @@ fof_status size_run(const fof_options &o, const int64_t *offsets, const double *
     return FOF_OK;
 }
 
-// The plan of a run in the context's workspace.
+// The plan of a run in the context's workspace. `beside_graph`: a run whose
+// box table a graph of several boxes, captured on the cells that the options
+// ask for, shares, keeps to those cells although the workspace has grown
+// since: an eager build of the captured geometry puts its table back.
 fof_status make_plan(const fof_ctx *c, const int64_t *offsets, const double *box, const double *lx, int32_t n_boxes,
-                     HostPlan *out)
+                     bool beside_graph, HostPlan *out)
 {
     if (!offsets || n_boxes < 1) return FOF_ERR_INVALID_ARG;
     HostPlan p;
     size_t need = 0;
     std::vector<AxisCells> axis((size_t)n_boxes);
-    const fof_status st = size_run(c->opt, offsets, box, lx, n_boxes, c->ws_bytes, axis.data(), &p, &need);
+    fof_status st = size_run(c->opt, offsets, box, lx, n_boxes, c->ws_bytes, axis.data(), &p, &need);
     if (st != FOF_OK) return st;
     p.boxes.resize((size_t)n_boxes);
     p.p0.assign(offsets, offsets + n_boxes + 1);
     p.lx_cells.assign(lx, lx + n_boxes);
-    int64_t cells = 0;
-    for (int32_t k = 0; k < n_boxes; ++k) {
-        BoxDev &b = p.boxes[(size_t)k];
-        const AxisCells &a = axis[(size_t)k];
-        box_geometry(box[k], lx[k], p.fine ? a.search : a.asked, cells, &b);
-        b.p0 = offsets[k];
-        b.p1 = offsets[k + 1];
-        if (c->opt.predicate == FOF_PRED_FP32_FILTER && b.use_fp64) ++p.fp64_boxes;
-        cells += cube(b.nc);
+    auto describe = [&]() {
+        int64_t cells = 0;
+        p.fp64_boxes = 0;
+        for (int32_t k = 0; k < n_boxes; ++k) {
+            BoxDev &b = p.boxes[(size_t)k];
+            const AxisCells &a = axis[(size_t)k];
+            box_geometry(box[k], lx[k], p.fine ? a.search : a.asked, cells, &b);
+            b.p0 = offsets[k];
+            b.p1 = offsets[k + 1];
+            if (c->opt.predicate == FOF_PRED_FP32_FILTER && b.use_fp64) ++p.fp64_boxes;
+            cells += cube(b.nc);
+        }
+    };
+    const HostPlan &g = c->graph_plan;
+    if (p.fine && beside_graph && c->exec && c->graph_boxes > 1 && !g.fine && g.p0 == p.p0) {
+        const Layout fine = p;
+        st = size_run(c->opt, offsets, box, lx, n_boxes, 0, nullptr, &p, &need);
+        if (st != FOF_OK) return st;
+        describe();
+        if (p.same_geometry(g)) {
+            *out = std::move(p);
+            return FOF_OK;
+        }
+        static_cast<Layout &>(p) = fine;
     }
+    describe();
     *out = std::move(p);
     return FOF_OK;
 }
@@ -696,7 +715,7 @@ void drop_graph(fof_ctx *c)
 }
 
 fof_status do_build(fof_ctx *c, const float *d_pos, const int64_t *off, const double *box, const double *lx,
-                    int32_t n_boxes)
+                    int32_t n_boxes, bool beside_graph)
 {
     if (c->opt.collect_timings && !c->timer) {
         if (ensure_device(c) != FOF_OK) return FOF_ERR_DEVICE;
@@ -704,7 +723,7 @@ fof_status do_build(fof_ctx *c, const float *d_pos, const int64_t *off, const do
         if (!c->timer || !c->timer->init()) return FOF_ERR_DEVICE;
     }
     HostPlan np;
-    fof_status st = make_plan(c, off, box, lx, n_boxes, &np);
+    fof_status st = make_plan(c, off, box, lx, n_boxes, beside_graph, &np);
     if (st != FOF_OK) return st;
     if (!d_pos && np.n > 0) return FOF_ERR_INVALID_ARG;
     st = install_plan(c, std::move(np));
@@ -869,7 +888,7 @@ fof_status fof_build_cells(fof_ctx *ctx, const float *d_pos, const int64_t *h_bo
 {
     if (!ctx) return FOF_ERR_INVALID_ARG;
     ctx->cells_valid = false;
-    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes);
+    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, true);
     if (st != FOF_OK) return st;
     st = enqueue_build(ctx, ctx->stream);
     ctx->state = st == FOF_OK ? 1 : 0;
@@ -984,7 +1003,7 @@ fof_status fof_graph_capture(fof_ctx *ctx, const float *d_pos, const int64_t *h_
 {
     if (!ctx) return FOF_ERR_INVALID_ARG;
     ctx->cells_valid = false;
-    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes);
+    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, false);
     if (st != FOF_OK) return st;
     if ((!d_group_index || !d_group_size) && ctx->plan.n > 0) return FOF_ERR_INVALID_ARG;
     ctx->dev.label = d_group_index;

@@ -145,3 +145,49 @@ def test_no_allocation_run_of_the_largest_size_held():
     ng = fof.fof_label_noalloc(pos, 1.0, lx, label, size, stream=torch.cuda.current_stream().cuda_stream)
     ref = fof.label(pos, lx)
     assert torch.equal(label, ref[0]) and torch.equal(size, ref[1]) and ng == ref[2]
+
+
+@pytest.mark.gpu
+def test_a_graph_of_several_boxes_outlives_a_larger_workspace():
+    """A larger size for the same workspace keeps the graph, and an eager run
+    of its geometry puts its box table back, although the same request alone
+    would now take subdivided cells; a new capture takes them."""
+    import torch
+
+    per, boxes, _, held = next(h for h in HELD if h[1] == 40)
+    off, lx = np.arange(boxes + 1, dtype=np.int64) * per, 0.2 / per ** (1.0 / 3.0)
+    pos_np = np.concatenate([synth.clustered(per, 13, k, 0.6) for k in range(boxes)])
+    pos = torch.from_numpy(pos_np).cuda()
+    ref = oracle.fof_boxes(pos_np, off, np.ones(boxes), np.full(boxes, lx))
+    f = fof.FoF()
+    try:
+        full = fof.fof_workspace_bytes(f.ctx, off, 1.0, lx)
+        f.ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+        label, size = f.outputs(len(pos_np))
+
+        def replay():
+            label.fill_(-7)
+            f.replay()
+            assert np.array_equal(f.n_groups(boxes), ref[2]) and np.array_equal(label.cpu().numpy(), ref[0])
+
+        fof.fof_set_workspace(f.ctx, f.ws, held)
+        fof.fof_graph_capture(f.ctx, pos, off, 1.0, lx, label, size)
+        replay()
+        cells = f.stats()["n_cells"]
+        fof.fof_set_workspace(f.ctx, f.ws, full)
+        replay()
+        eager = f.run(pos, off, 1.0, lx)
+        assert np.array_equal(eager[0].cpu().numpy(), ref[0])
+        replay()
+        f.run(pos[: 5 * per].contiguous(), off[:6], 1.0, lx)
+        with pytest.raises(fof.FoFError) as e:
+            f.replay()
+        assert e.value.status == fof.FOF_ERR_BAD_STATE
+        f.run(pos, off, 1.0, lx)
+        replay()
+        assert f.stats()["n_cells"] == cells
+        fof.fof_graph_capture(f.ctx, pos, off, 1.0, lx, label, size)
+        replay()
+        assert f.stats()["n_cells"] > cells
+    finally:
+        f.close()
