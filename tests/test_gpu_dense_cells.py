@@ -111,3 +111,65 @@ def test_subdivided_cells_and_a_workspace_that_only_holds_the_coarse_ones(predic
     finally:
         coarse.close()
         auto.close()
+
+
+def bridged_cells(rng, axis, wrap):
+    """Two neighbouring cells of 300 particles, each one set of touching
+    sub-cells (a blob, a few particles half way and one near the face), whose
+    only link is the pair of particles near the face; and the indices of that pair."""
+    h = 1.0 / 8
+    face = 0.0 if wrap else 4 * h
+    out, at = [], []
+    for side in (-1, 1):
+        depth = np.full(300, 0.08)
+        depth[rng.permutation(300)[:6]] = 0.065   # 0.095 from the other cell's nearest particle
+        k = int(rng.integers(300))
+        depth[k] = 0.03
+        cell = np.full((300, 3), 3.5 * h) + 0.004 * (rng.random((300, 3)) - 0.5)
+        cell[:, axis] = face + side * depth + 0.0005 * (rng.random(300) - 0.5)
+        at.append(k + 300 * len(out))
+        out.append(cell)
+    return (np.concatenate(out) % 1.0).astype(np.float32), at
+
+
+def touching_sets(sub):
+    """Number of sets of touching sub-cells (27-neighbourhood) among the rows of `sub`."""
+    left, sets = set(map(tuple, sub)), 0
+    while left:
+        todo, sets = [left.pop()], sets + 1
+        while todo:
+            c = np.array(todo.pop())
+            for d in np.ndindex(3, 3, 3):
+                t = tuple(c + np.array(d) - 1)
+                if t in left:
+                    left.remove(t)
+                    todo.append(t)
+    return sets
+
+
+@pytest.mark.parametrize("predicate", ["fp32_filter", "fp64"])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("wrap", [False, True])
+def test_one_bridge_between_two_cells_of_one_group_each(axis, wrap, predicate):
+    """Cells that the pre-merge finds to be one group: a neighbour is sampled
+    first, and what the sample misses has to be found in the rest of it."""
+    opt = dict(cell_factor=1.375, dense_min=8)
+    info = fof.fof_describe_box(600, 1.0, LX, fof.make_options(**opt))
+    nc, k = info["cells_per_axis"], info["sub_cells_per_axis"]
+    assert nc == 8 and info["sub_cells_adjacent"]
+    for seed in range(12):
+        rng = np.random.default_rng(100 * seed + 10 * axis + wrap)
+        pos, bridge = bridged_cells(rng, axis, wrap)
+        cell = np.floor(pos.astype(np.float64) * nc).astype(int)
+        sub = np.floor((pos.astype(np.float64) * nc - cell) * k).astype(int)
+        cells = np.unique(cell, axis=0)
+        assert len(cells) == 2
+        for c in cells:
+            mine = (cell == c).all(axis=1)
+            assert mine.sum() == 300 and touching_sets(sub[mine]) == 1
+        for cut in (False, True):
+            p = np.delete(pos, bridge[1], axis=0) if cut else pos
+            ref = oracle.fof(p, LX)
+            assert ref[2] == (2 if cut else 1)
+            got = run(p, predicate=predicate, **opt)
+            assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]) and got[2] == ref[2], (seed, cut)
