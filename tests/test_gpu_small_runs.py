@@ -86,3 +86,45 @@ def test_coordinates_are_checked_in_every_build(n):
             f.run(pos, [0, n], 1.0, lx)
     finally:
         f.close()
+
+
+@pytest.mark.parametrize("sizes", [[900_000], [900_001], [500_000, 3, 399_997], [500_000, 3, 399_998]])
+def test_both_sides_of_the_one_level_sort(sizes):
+    """At 9e5 particles the placement, the way of the results and the group counts all change."""
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    lx = np.array([synth.linking_length(0.2, s) if s > 8 else 0.1 for s in sizes])
+    p = np.concatenate([synth.clustered(s, 70, k, 0.3) for k, s in enumerate(sizes)])
+    pos = torch.from_numpy(p).cuda()
+    refs = [[oracle.fof_parallel(p[offsets[k]:offsets[k + 1]], scale * lx[k], threads=8) for k in range(len(sizes))]
+            for scale in (1.0, 0.7)]
+    for predicate in ("fp32_filter", "fp64"):
+        f = fof.FoF(predicate)
+        try:
+            for scale, ref in zip((1.0, 0.7), refs):
+                got = f.run(pos, offsets, 1.0, lx) if scale == 1.0 else f.relink(scale * lx, len(sizes))
+                assert np.array_equal(got[0].cpu().numpy(), np.concatenate([r[0] for r in ref])), (predicate, scale)
+                assert np.array_equal(got[1].cpu().numpy(), np.concatenate([r[1] for r in ref])), (predicate, scale)
+                assert np.array_equal(got[2], [r[2] for r in ref]), (predicate, scale)
+        finally:
+            f.close()
+
+
+@pytest.mark.parametrize("n", [50_000, 200_000])   # tiles that sum their counts, and tiles that take atomics
+@pytest.mark.parametrize("boxes", [1, 2])
+def test_1024_and_1025_segments(n, boxes):
+    """64^3 cells are 1024 segments of 2^8, the most that one level sorts; the
+    27 cells of a second box make one more."""
+    sizes = [n, 5][:boxes]
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    lx = np.array([synth.linking_length(0.2, n), 0.3])[:boxes]
+    opt = dict(cell_factor=1.0 / (lx[0] * 64.5), segment_log2=8)
+    p = np.concatenate([synth.clustered(s, 80, k, 0.6) for k, s in enumerate(sizes)])
+    ref = oracle.fof_boxes(p, offsets, np.ones(boxes), lx)
+    f = fof.FoF(**opt)
+    try:
+        got = f.run(torch.from_numpy(p).cuda(), offsets, 1.0, lx)
+        assert f.stats()["n_cells"] == 64 ** 3 + 27 * (boxes - 1)
+        assert np.array_equal(got[0].cpu().numpy(), ref[0]) and np.array_equal(got[1].cpu().numpy(), ref[1])
+        assert np.array_equal(got[2], ref[2])
+    finally:
+        f.close()
