@@ -123,9 +123,12 @@ def test_runs_in_the_least_workspace(per, boxes, kw, held):
                 fof.fof_relink(f.ctx, scale * lx, boxes)
             fof.fof_link(f.ctx)
             ng = fof.fof_finalize(f.ctx, label, size, boxes)
-            ref = oracle.fof_boxes(pos_np, off, np.ones(boxes), np.full(boxes, scale * lx))
+            if boxes == 1:
+                ref = oracle.fof_parallel(pos_np, scale * lx, threads=8)
+            else:
+                ref = oracle.fof_boxes(pos_np, off, np.ones(boxes), np.full(boxes, scale * lx))
             assert np.array_equal(label.cpu().numpy(), ref[0]) and np.array_equal(size.cpu().numpy(), ref[1])
-            assert np.array_equal(ng, ref[2])
+            assert np.array_equal(ng, np.atleast_1d(ref[2]))
             first, gsize, box = f.catalogue(label, size, 2)
             at = np.flatnonzero(ref[1] >= 2)
             assert np.array_equal(first.cpu().numpy(), ref[0][at]) and np.array_equal(gsize.cpu().numpy(), ref[1][at])
