@@ -6,6 +6,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <vector>
 
@@ -171,6 +172,18 @@ struct fof_ctx {
 };
 
 namespace {
+
+// Runs an entry point's work: a failed host allocation is a status, no
+// exception leaves the library.
+template <typename Work>
+fof_status no_throw(Work &&work)
+{
+    try {
+        return work();
+    } catch (const std::exception &) {
+        return FOF_ERR_DEVICE;
+    }
+}
 
 fof_status dev_err(hipError_t e) { return e == hipSuccess ? FOF_OK : FOF_ERR_DEVICE; }
 
@@ -671,6 +684,8 @@ fof_status upload_table(fof_ctx *c, const HostPlan &np)
         if (hipHostMalloc(&c->stage[k], table, hipHostMallocDefault) != hipSuccess) return FOF_ERR_DEVICE;
         c->stage_bytes[k] = table;
     }
+    c->table_id = 0;   // no known table until this one is in
+    c->table_plan = np;
     std::memset(c->stage[k], 0, table);
     std::memcpy(at<char>(c->stage[k], np.o_boxes), np.boxes.data(), sizeof(BoxDev) * np.boxes.size());
     std::memcpy(at<char>(c->stage[k], np.o_p0), np.p0.data(), sizeof(int64_t) * np.p0.size());
@@ -679,7 +694,6 @@ fof_status upload_table(fof_ctx *c, const HostPlan &np)
     if (hipEventRecord(c->stage_done[k], c->stream) != hipSuccess) return FOF_ERR_DEVICE;
     c->stage_pending[k] = true;
     c->stage_next = k ^ 1;
-    c->table_plan = np;
     c->table_id = ++c->upload_seq;
     return FOF_OK;
 }
@@ -759,7 +773,11 @@ fof_status read_device(fof_ctx *c, const void *d_src, size_t bytes, bool busy, c
         if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     if (c->read_bytes < bytes) {
-        c->pageable.resize(bytes);
+        const fof_status st = no_throw([&] {
+            c->pageable.resize(bytes);
+            return FOF_OK;
+        });
+        if (st != FOF_OK) return st;
         to = c->pageable.data();
     }
     if (c->reads < kEarlyReads) ++c->reads;
@@ -888,7 +906,7 @@ fof_status fof_build_cells(fof_ctx *ctx, const float *d_pos, const int64_t *h_bo
 {
     if (!ctx) return FOF_ERR_INVALID_ARG;
     ctx->cells_valid = false;
-    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, true);
+    fof_status st = no_throw([&] { return do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, true); });
     if (st != FOF_OK) return st;
     st = enqueue_build(ctx, ctx->stream);
     ctx->state = st == FOF_OK ? 1 : 0;
@@ -914,8 +932,9 @@ fof_status fof_relink(fof_ctx *ctx, const double *h_lx, int32_t n_boxes)
         if (ctx->opt.predicate == FOF_PRED_FP32_FILTER && b.use_fp64) ++p.fp64_boxes;
     }
     ctx->dev.box0 = p.boxes[0];
+    ctx->state = 0;   // should the table not follow the new lengths
     if (p.n_boxes > 1) {
-        fof_status st = upload_table(ctx, p);
+        fof_status st = no_throw([&] { return upload_table(ctx, p); });
         if (st != FOF_OK) return st;
     }
     fof_status st = dev_err(fof::launch_relink_reset(ctx->dev, ctx->stream));
@@ -977,9 +996,12 @@ fof_status fof_get_stats(fof_ctx *ctx, fof_stats *out)
     if (!ctx || !out) return FOF_ERR_INVALID_ARG;
     std::memset(out, 0, sizeof(*out));
     if (!ctx->planned) return FOF_ERR_BAD_STATE;
-    std::vector<int64_t> g((size_t)ctx->plan.n_boxes);
+    std::vector<int64_t> g;
     Counters cnt{};
-    fof_status st = read_back(ctx, g.data(), &cnt);
+    fof_status st = no_throw([&] {
+        g.resize((size_t)ctx->plan.n_boxes);
+        return read_back(ctx, g.data(), &cnt);
+    });
     out->n_particles = ctx->plan.n;
     out->n_cells = ctx->plan.n_cells;
     for (int64_t v : g) out->n_groups += v;
@@ -1003,12 +1025,17 @@ fof_status fof_graph_capture(fof_ctx *ctx, const float *d_pos, const int64_t *h_
 {
     if (!ctx) return FOF_ERR_INVALID_ARG;
     ctx->cells_valid = false;
-    fof_status st = do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, false);
+    fof_status st = no_throw([&] { return do_build(ctx, d_pos, h_box_offsets, h_box, h_lx, n_boxes, false); });
     if (st != FOF_OK) return st;
     if ((!d_group_index || !d_group_size) && ctx->plan.n > 0) return FOF_ERR_INVALID_ARG;
     ctx->dev.label = d_group_index;
     ctx->dev.size = d_group_size;
     drop_graph(ctx);
+    st = no_throw([&] {
+        ctx->graph_plan = ctx->plan;
+        return FOF_OK;
+    });
+    if (st != FOF_OK) return st;
     // the descriptor upload above is ordered on ctx->stream; capture on a
     // private stream that first waits for it
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return FOF_ERR_DEVICE;
@@ -1031,12 +1058,8 @@ fof_status fof_graph_capture(fof_ctx *ctx, const float *d_pos, const int64_t *h_
         if (e == hipSuccess) {
             ctx->graph = g;
             e = hipGraphInstantiate(&ctx->exec, g, nullptr, nullptr, 0);
-            if (e == hipSuccess) {
-                ctx->graph_boxes = ctx->plan.n_boxes;
-                ctx->graph_plan = ctx->plan;
-            } else {
-                drop_graph(ctx);
-            }
+            if (e == hipSuccess) ctx->graph_boxes = ctx->plan.n_boxes;
+            else drop_graph(ctx);
         } else if (g) {
             (void)hipGraphDestroy(g);
         }

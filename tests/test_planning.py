@@ -2,6 +2,9 @@
 workspaces hold which runs."""
 from __future__ import annotations
 
+import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -194,3 +197,32 @@ def test_a_graph_of_several_boxes_outlives_a_larger_workspace():
         assert f.stats()["n_cells"] > cells
     finally:
         f.close()
+
+
+OUT_OF_MEMORY = """
+import ctypes, resource, sys
+import numpy as np
+sys.path.insert(0, {root!r})
+import paper_2003_11468_amd as fof
+fof.load_library()
+nb = 4_000_000   # empty boxes: their descriptors alone take 0.4 GB
+off, side, lx = np.zeros(nb + 1, dtype=np.int64), np.ones(nb), np.full(nb, 0.3)
+ctx = fof.fof_create(fof.make_options(cell_factor={factor}))
+fof._check(fof.load_library().fof_set_workspace(ctx, ctypes.c_void_p(1 << 20), 1 << 50), "fof_set_workspace")
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (150 << 20), resource.RLIM_INFINITY))
+for call in (fof.fof_build_cells, lambda *a: fof.fof_graph_capture(*a, None, None)):
+    try:
+        call(ctx, None, off, side, lx)
+    except fof.FoFError as e:
+        print("status", e.status)
+"""
+
+
+@pytest.mark.parametrize("factor", [0.0, 3.0])
+def test_no_exception_leaves_the_library_when_host_memory_runs_out(factor):
+    """The planning of a batch allocates; a failed allocation is a status, not an abort of the process."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", OUT_OF_MEMORY.format(root=root, factor=factor)], capture_output=True,
+                       text=True, env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"), timeout=100)
+    assert (r.returncode, r.stdout.split()) == (0, ["status", str(fof.FOF_ERR_DEVICE)] * 2), r.stderr[-500:]
