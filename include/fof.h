@@ -67,7 +67,8 @@ typedef enum {
     FOF_ERR_OUT_OF_BOX = 2,    /* a coordinate not finite or outside [0, L) (latched on the device) */
     FOF_ERR_BAD_STATE = 3,     /* calls out of order (link before build, finalize before link) */
     FOF_ERR_WORKSPACE = 4,     /* workspace missing, too small or misaligned */
-    FOF_ERR_DEVICE = 5,        /* a HIP runtime call failed, or a device-side consistency check */
+    FOF_ERR_DEVICE = 5,        /* a HIP runtime call or a host allocation failed, or a device-side
+                                  consistency check */
     FOF_ERR_UNSUPPORTED = 6    /* valid request the library cannot serve (e.g. too many cells) */
 } fof_status;
 
@@ -83,13 +84,19 @@ typedef struct {
                                 particle each, never narrower than l_x, which the search
                                 subdivides where they are much wider than l_x and the limits and
                                 the workspace allow (changes speed only) */
-    int32_t collect_stats;   /* 1: count pair tests, links, band hits, CAS retries (slower) */
+    int32_t collect_stats;   /* 1: count pair tests, links, band hits, CAS retries. A slower form of the
+                                search: every step of the link pass is a launch of its own, and the
+                                wavefront search tests every candidate and merges at every link (it
+                                passes over no group already joined and gathers no links first), so
+                                its pair_tests and cas_retries are above those of a run without */
     int32_t dense_min;       /* cells holding at least this many particles are searched by whole
                                 wavefronts (64 particles against broadcast candidates); the others
                                 per particle. 0 = default (32; 8 where the search subdivides
                                 automatic cells) */
     int32_t collect_timings; /* 1: record HIP events around every kernel launch on the context's
-                                stream (read with fof_get_kernel_times) */
+                                stream (read with fof_get_kernel_times). Every run then takes the
+                                launches of a large one, so that each step is timed on its own;
+                                without it, runs of up to 9e5 particles take fewer and fused ones */
     int32_t sort_segment_log2; /* the cell sort takes 2^k consecutive cells per work-group (their
                                 occupancy bits and the counts of the occupied cells in on-chip
                                 memory): k in 6..16; 0 = automatic (about 1.4k particles per
@@ -154,8 +161,9 @@ typedef struct {
     float hi32;              /* FP32 squared distance above this: not linked, proven */
     int32_t fp64_only;       /* 1: the FP32 filter cannot be proven for this box; every pair is
                                 decided in double */
-    int32_t sub_cells_per_axis; /* k: dense cells are pre-merged by k^3 sub-cells whose diagonal is
-                                at most l_x (1 - 1e-6); 0 = no pre-merge */
+    int32_t sub_cells_per_axis; /* k: of these cells, dense ones are pre-merged by k^3 sub-cells whose
+                                diagonal is at most l_x (1 - 1e-6); 0 = no pre-merge. (Where the search
+                                subdivides automatic cells, its own cells have their own k.) */
     int32_t sub_cells_adjacent; /* 1: the sub-cells are small enough (2 sqrt(3) s <= l_x (1 - 1e-6),
                                 s their side) that any two points of two touching sub-cells are
                                 linked, and touching occupied sub-cells are merged too */
@@ -207,7 +215,12 @@ fof_status fof_create(fof_ctx **out, const fof_options *opt, void *hip_stream);
 fof_status fof_set_stream(fof_ctx *ctx, void *hip_stream);
 
 /* Host only, touches no device memory: validates the box description and
- * returns in *bytes the workspace the following fof_build_cells needs.
+ * returns in *bytes the workspace the following fof_build_cells needs to run
+ * at full speed. With automatic cells that includes their subdivision
+ * (fof_options.cell_factor); a smaller workspace is taken too as long as it
+ * holds the run on the cells that fof_describe_box gives (7 to 13 % less at
+ * b = 0.2), on which the search then stays: several times slower where
+ * particles crowd. fof_stats.n_cells tells which were taken.
  * h_box_offsets has n_boxes + 1 non-decreasing entries starting at 0; the
  * total count must be below 2^31. Each box needs L > 0 finite, 0 < l_x and at
  * least 3 cells of side >= l_x (1 + 2^-20) per axis (so l_x < L / 3).
@@ -301,9 +314,11 @@ fof_status fof_graph_launch(fof_ctx *ctx);
  * Errors, all before any device work: FOF_ERR_INVALID_ARG (bad options,
  * collect_timings set, n < 0 or > 2^31 - 1, a null pointer with n > 0, bad
  * box or linking length), FOF_ERR_UNSUPPORTED (the run needs more than
- * FOF_NOALLOC_SCRATCH_BYTES -- fof_workspace_bytes gives the need for the
- * same options and box -- or too many cells); FOF_ERR_DEVICE (no device, or
- * the scratch address could not be found). */
+ * FOF_NOALLOC_SCRATCH_BYTES, or too many cells); FOF_ERR_DEVICE (no device, or
+ * the scratch address could not be found). What fof_workspace_bytes gives for
+ * the same options and box is enough; with automatic cells a run of which it
+ * gives more is still taken while the cells of fof_describe_box fit, without
+ * their subdivision (at b = 0.2 from 1.30e6 to 1.49e6 particles). */
 fof_status fof_label_noalloc(const fof_options *opt, void *hip_stream, const float *d_pos, int64_t n, double box,
                              double lx, int32_t *d_group_index, int32_t *d_group_size, int64_t *h_n_groups);
 

@@ -660,10 +660,11 @@ __device__ __forceinline__ void sparse_search(const Plan &p, SparseLds &L, int b
             // every row that holds k takes in row k. Afterwards row u is u's
             // component, and its lowest bit the component's smallest slot,
             // the node of smallest hooking key, under which u is hooked.
-            // Every particle is still its own root while the search runs,
-            // unless a full edge-list slice made a search merge its surplus
-            // at once: so the hook is a compare-and-swap, and one that finds
-            // its slot hooked already becomes an ordinary union.
+            // A particle may have been hooked by then: with kInline the waves
+            // merge their pairs all through the search, otherwise only where
+            // a full edge-list slice made a search merge its surplus at once.
+            // So the hook is a compare-and-swap, and one that finds its slot
+            // hooked already becomes an ordinary union.
             const unsigned long long tile_links = L.adj[lane];
             const unsigned long long todo = __ballot(tile_links != 0ull);
             if (todo) {
@@ -1403,10 +1404,11 @@ __global__ void __launch_bounds__(kBlock) k_link_dense(Plan p)
 // search from 157 to 54 us. A larger cell is split into k^3 sub-cells small enough that any two
 // particles of one sub-cell are linked. When the sub-cells are smaller still (sub_adj:
 // any two particles of two sub-cells that touch, across a face, an edge or a
-// corner, are linked), a union-find over the occupied sub-cells in LDS joins
-// every two touching occupied sub-cells. Every particle is then hooked
-// straight under the particle of highest hooking priority (smallest key) of
-// its sub-cell or joined set: only particles joined by chains of linked pairs
+// corner, are linked), every two touching occupied sub-cells are joined: up to
+// 64 occupied ones by the closure of their rows of touching ones, more on a
+// grid of up to 128 by growing components of one mask, else by a union-find in
+// LDS. Every particle is then hooked straight under the particle of highest
+// hooking priority (smallest key) of its sub-cell or joined set: only particles joined by chains of linked pairs
 // are merged, so the groups are unchanged, and the pair search meets few
 // groups per dense cell (its staging drops the candidates of the home
 // particles' own group). The particles of dense cells are still their own
