@@ -1,14 +1,17 @@
 """Autotuner for the launch parameters of the labelling pipeline.
 
 Cell size and tile shape:
-- cell_factor: cell side in units of l_x (>= 1; 0 = about one particle per
-  cell). Smaller cells test fewer pairs inside dense groups but cost more
+- cell_factor: cell side in units of l_x (>= 1; 0 = automatic: cells of about
+  one particle, which the search subdivides to 1.375 l_x where they are wider,
+  so it is 1.375 again unless cells of one particle are narrower or more than
+  64 cells would fall on a particle). Smaller cells test fewer pairs inside dense groups but cost more
   cell bookkeeping; the best value depends on the clustering.
 - dense_min: cells with at least this many particles are searched by whole
   wavefronts (tiles of 64 home particles against 64 staged candidates), the
   others by the load-balanced per-particle search (tiles of 64 home
   particles, each with its own candidate ranges).
-- segment_log2: cells per work-group of the in-LDS cell sort (0: automatic).
+- segment_log2: cells per work-group of the in-LDS cell sort (0: automatic),
+  counted before automatic cells are subdivided.
 Work schedule and contention variants:
 - schedule: work-groups of the two persistent link kernels, whether dense
   cells are pre-merged by sub-cells, the giant-component skip, and whether
